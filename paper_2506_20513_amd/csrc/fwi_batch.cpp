@@ -79,15 +79,26 @@ struct Problem {
 
 hipError_t ok(int rc) { return rc == FWI_OK ? hipSuccess : hipErrorUnknown; }
 
-// Temporal depth of the passes and row bands of height `rows` (0 = the
-// single-problem heuristic for that depth).  The checkpoint interval is a
-// multiple of both depths, so the workspace layout does not change.
-void set_tiling(Layout &L, int depth, int rows) {
-    L.depth = depth;
-    if (rows <= 0)
-        make_tiling(L.d, L);
-    else
-        fixed_bands(L, rows, depth);
+// Temporal depth of the passes and row bands of height `rows`.  0: tiles of
+// one height for all problems (their passes share launches), the imaging sums
+// grouped by `depth`, or for a batch too large for them the streaming default
+// of each problem.  The checkpoint interval is a multiple of both depths, so
+// the workspace layout does not change.
+void set_tiling(std::vector<Problem> &probs, int depth, int rows) {
+    long long tiles = 0, cells = 0;
+    for (const Problem &p : probs) {
+        tiles += tile_count(p.d);
+        cells += (long long)p.d.S * p.d.NX * p.d.NY;
+    }
+    for (Problem &p : probs) {
+        p.L.depth = depth;
+        if (rows > 0)
+            fixed_bands(p.L, rows, depth);
+        else if (use_tiles(cells))
+            set_tiles(p.L, pick_tile(tiles));
+        else
+            set_streams(p.L);
+    }
 }
 
 // The operations of one problem's gradient, in its own order, with keys.
@@ -124,7 +135,7 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
     };
     const size_t field = (size_t)d.S * d.plane;
     const size_t fbytes = field * sizeof(float);
-    const int D = L.depth;
+    const int D = L.pass;
     float *Ca = P.f(L.off_Ca), *Cs = P.f(L.off_Cs);
     const State fs[2] = {P.state(L.off_fwd[0], false), P.state(L.off_fwd[1], false)};
     const State as[2] = {P.state(L.off_adj[0], true), P.state(L.off_adj[1], true)};
@@ -160,6 +171,8 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
             a.Hy_in = fs[cur].Hy;
             a.Hx_out = fs[cur ^ 1].Hx;
             a.Hy_out = fs[cur ^ 1].Hy;
+            a.psi_in = fs[cur].phx;
+            a.psi_out = fs[cur ^ 1].phx;
             Op o;
             o.key = {{1, n, 1, 0}};
             o.kind = OP_FWD;
@@ -209,6 +222,8 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
             f.Hy_in = fs[fcur].Hy;
             f.Hx_out = fs[fcur ^ 1].Hx;
             f.Hy_out = fs[fcur ^ 1].Hy;
+            f.psi_in = fs[fcur].phx;
+            f.psi_out = fs[fcur ^ 1].phx;
             Op o;
             o.key = {{4, X, 1, j}};
             o.kind = OP_FWD;
@@ -231,6 +246,8 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
             b.L_out = as[acur ^ 1].E;
             b.LHx_out = as[acur ^ 1].Hx;
             b.LHy_out = as[acur ^ 1].Hy;
+            b.psi_in = as[acur].phx;
+            b.psi_out = as[acur ^ 1].phx;
             Op o;
             o.key = {{4, X, 2, j}};
             o.kind = OP_ADJ;
@@ -341,14 +358,16 @@ void build_schedule(std::vector<Problem> &probs, char *ws, size_t area, Schedule
         while (j < ops.size() && ops[j].kind == o.kind && ops[j].key == o.key) ++j;
         // full-depth and partial passes go to separate launches, and so do
         // forward passes that write every level's Ez and those that do not
-        const int depth = o.kind == OP_FWD ? o.fa.tl.depth : o.aa.tl.depth;
+        const Tiling &ot = o.kind == OP_FWD ? o.fa.tl : o.aa.tl;
+        const int depth = ot.depth;
         for (int part = 0; part < 4; ++part) {
             const int tail = part & 1, lev = part >> 1;
             if (o.kind == OP_ADJ && lev) continue;
+            if (ot.tile && tail) continue;        // tiles take every number of levels
             Step s;
             s.kind = o.kind;
             s.tail = tail != 0;
-            s.depth = depth;
+            s.depth = table_depth(ot);
             s.lev = lev;
             s.nm = 0;
             s.nblocks = 0;
@@ -360,7 +379,7 @@ void build_schedule(std::vector<Problem> &probs, char *ws, size_t area, Schedule
             for (size_t k = i; k < j; ++k) {
                 const Op &q = ops[k];
                 const int nlev = q.kind == OP_FWD ? q.fa.nlev : q.aa.nlev;
-                if ((nlev < depth) != (tail != 0)) continue;
+                if (!ot.tile && (nlev < depth) != (tail != 0)) continue;
                 if (q.kind == OP_FWD && (q.fa.E_lev != nullptr) != (lev != 0)) continue;
                 const Tiling &tl = q.kind == OP_FWD ? q.fa.tl : q.aa.tl;
                 const int Sq = q.kind == OP_FWD ? q.fa.S : q.aa.S;
@@ -394,7 +413,8 @@ hipError_t run_step(const Step &s, char *ws, hipStream_t st) {
                             s.nm, s.nblocks, s.depth, s.tail, st);
 }
 
-int upload_tables(const Schedule &S, char *ws, hipStream_t st) {
+int upload_tables(const Schedule &S, size_t area, char *ws, hipStream_t st) {
+    if (S.bytes > area) return FWI_ENOMEM;     // would overwrite the problems' layouts
     if (!S.ftab.empty())
         FWI_TRY(hipMemcpyAsync(ws + S.f_off, S.ftab.data(), S.ftab.size() * sizeof(FwdStreamArgs),
                                hipMemcpyHostToDevice, st));
@@ -458,6 +478,17 @@ size_t place(std::vector<Problem> &probs, size_t area_end) {
     return off;
 }
 
+// Bytes of the plan tables at the workspace's start, enough for every
+// candidate: the streaming passes at depth 4 are the most there can be.
+// Layout offsets do not change the table sizes: counted with a null base.
+size_t table_area(std::vector<Problem> &probs) {
+    set_tiling(probs, kDepthSmall, 1 << 20);
+    Schedule S;
+    place(probs, 0);
+    build_schedule(probs, nullptr, 0, S);
+    return S.bytes;
+}
+
 }  // namespace batch
 }  // namespace fwi
 
@@ -483,13 +514,7 @@ extern "C" int fwi_batch_workspace_bytes(int32_t n, const fwi_batch_problem *pro
     int K = 0;
     int rc = batch::prepare(n, problems, probs, K);
     if (rc != FWI_OK) return rc;
-    for (Problem &p : probs) set_tiling(p.L, kDepthSmall, 0);
-    Schedule S;
-    // layout offsets do not change the table sizes: count with a null base;
-    // depth 4 has the most passes, so its tables are the largest
-    place(probs, 0);
-    build_schedule(probs, nullptr, 0, S);
-    *bytes = place(probs, S.bytes);
+    *bytes = place(probs, table_area(probs));
     return FWI_OK;
 }
 
@@ -503,11 +528,9 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
     int K = 0;
     int rc = batch::prepare(n, problems, probs, K);
     if (rc != FWI_OK) return rc;
-    for (Problem &p : probs) set_tiling(p.L, kDepthSmall, 0);
+    const size_t area = table_area(probs);
+    const size_t need = place(probs, area);
     Schedule S;
-    place(probs, 0);
-    build_schedule(probs, nullptr, 0, S);
-    const size_t need = place(probs, S.bytes);
     if (!ws || (reinterpret_cast<uintptr_t>(ws) % kAlign) != 0 || ws_bytes < need)
         return FWI_ENOMEM;
     fwi_batch_plan *plan = new (std::nothrow) fwi_batch_plan;
@@ -585,11 +608,11 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
         int tuned = 0;
         for (int dep : depths) {
             for (int h : heights) {
-                for (Problem &p : probs) set_tiling(p.L, dep, h);
+                set_tiling(probs, dep, h);
                 rc = upload_all();
                 if (rc != FWI_OK) break;
                 build_schedule(probs, w, 0, S);
-                rc = upload_tables(S, w, st);
+                rc = upload_tables(S, area, w, st);
                 if (rc != FWI_OK) break;
                 // run the set-up steps once so the first pass reads valid state
                 size_t first = 0;
@@ -648,11 +671,11 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
         (void)hipEventDestroy(e1);
         if (rc != FWI_OK) return fail(rc);
     }
-    for (Problem &p : probs) set_tiling(p.L, depth, rows);
+    set_tiling(probs, depth, rows);
     rc = upload_all();
     if (rc != FWI_OK) return fail(rc);
     build_schedule(probs, w, 0, S);
-    rc = upload_tables(S, w, st);
+    rc = upload_tables(S, area, w, st);
     if (rc != FWI_OK) return fail(rc);
 
     // capture the whole sequence once, on a private stream (the caller's may

@@ -141,18 +141,65 @@ int pick_bands(const Dims &d, int K, int nstrip, double waves, int *bands, int g
 constexpr double kFwdWaves = 4.0;
 double adj_waves(int depth) { return depth == kDepthLarge ? 3.0 : 4.0; }
 
-void make_tiling(const Dims &d, Layout &L, int groups) {
+// Tiles or streams.  The streaming kernels read a field row once per pass and
+// pay a load latency per row; the tile kernels read a tile with its halo (1.8
+// times its cells) at once.  Up to kTileCells cells (all shots of the call)
+// the fields of a pass fit the 256 MB last-level cache or the chip is not full
+// of waves, and tiles are faster: one gradient took (streams -> tiles)
+// 148 x 148 x 1 shot, 800 steps: 19.4 -> 4.5 ms; 552 x 296 x 24 shots, 3000
+// steps: 146 -> 123 ms; 1040 x 640 x 24 shots (16 M cells), 96 steps:
+// 16.6 -> 15.3 ms; 2088 x 1064 x 4 shots (9 M), 96 steps: 9.6 -> 8.6 ms, but
+// with 16 shots (36 M) 27.7 -> 31.4 ms.
+constexpr long long kTileCells = 20LL << 20;
+
+bool use_tiles(long long cells) { return cells <= kTileCells; }
+
+long long tile_count(const Dims &d) {
+    constexpr int OX = 64 - 2 * kTileLevels, OY = kTileRowsLarge - 2 * kTileLevels;
+    return (long long)d.S * ((d.NX + OX - 1) / OX) * ((d.NY + OY - 1) / OY);
+}
+
+// Tall tiles recompute less (1.8 against 2.7 times the cells), low ones spread
+// a small problem over more CUs.  Per gradient of 160 steps (low / tall):
+// 148 x 148 cells, 1 shot (16 tall tiles): 1.10 / 1.29 ms, 8 shots (128):
+// 1.33 / 1.36, 15 shots (240): 1.82 / 1.40; 552 x 296, 2 shots (168), 240
+// steps: 1.97 / 2.08, 6 shots (504): 4.3 / 3.4.
+int pick_tile(long long tiles) { return tiles <= 192 ? kTileRowsSmall : kTileRowsLarge; }
+
+void set_tiles(Layout &L, int rows) {
+    const int OX = 64 - 2 * kTileLevels, OY = rows - 2 * kTileLevels;
+    L.tile = rows;
+    L.pass = kTileLevels;
+    L.nstrip = (L.d.NX + OX - 1) / OX;
+    L.nband = L.naband = (L.d.NY + OY - 1) / OY;
+    L.bands[0] = L.abands[0] = 0;          // the tile kernels use no band table
+}
+
+void set_streams(Layout &L, int groups) {
     static_assert(sizeof(L.bands) / sizeof(int) == 64 && sizeof(L.abands) / sizeof(int) == 64,
                   "band tables hold 63 bands");
     const int K = L.depth, OW = 64 - 2 * K;
-    L.nstrip = (d.NX + OW - 1) / OW;
-    L.nband = pick_bands(d, K, L.nstrip, kFwdWaves, L.bands, groups);
-    L.naband = pick_bands(d, K, L.nstrip, adj_waves(K), L.abands, groups);
+    L.tile = 0;
+    L.pass = K;
+    L.nstrip = (L.d.NX + OW - 1) / OW;
+    L.nband = pick_bands(L.d, K, L.nstrip, kFwdWaves, L.bands, groups);
+    L.naband = pick_bands(L.d, K, L.nstrip, adj_waves(K), L.abands, groups);
+}
+
+// The layout's decomposition, one of `groups` launches of its kind that share
+// the chip.
+void make_tiling(const Dims &d, Layout &L, int groups) {
+    if (use_tiles((long long)groups * d.S * d.NX * d.NY))
+        set_tiles(L, pick_tile(groups * tile_count(d)));
+    else
+        set_streams(L, groups);
 }
 
 void fixed_bands(Layout &L, int rows, int depth) {
     const int OW = 64 - 2 * depth;
     const int max_bands = (int)(sizeof(L.bands) / sizeof(int)) - 1;
+    L.tile = 0;
+    L.pass = depth;
     L.nstrip = (L.d.NX + OW - 1) / OW;
     const int h = std::max(rows, (L.d.NY + max_bands - 1) / max_bands);
     int nb = 0;
@@ -427,7 +474,8 @@ Tiling tiling(const Ptrs &P) {
     t.bands = P.i(L.off_bands);
     t.nstrip = L.nstrip;
     t.nband = L.nband;
-    t.depth = L.depth;
+    t.depth = L.pass;
+    t.tile = L.tile;
     return t;
 }
 
@@ -483,6 +531,9 @@ FwdStreamArgs fwd_args(const Ptrs &P) {
     a.E_in = nullptr; a.E_out = nullptr; a.E_lev = nullptr;
     a.Hx_in = a.Hy_in = nullptr;
     a.Hx_out = a.Hy_out = nullptr;
+    a.psi_in = a.psi_out = nullptr;
+    a.psi_y = align_up((size_t)d.S * d.ys * sizeof(float)) / sizeof(float);
+    a.psi_x = align_up((size_t)d.S * d.xs * sizeof(float)) / sizeof(float);
     a.cold = reinterpret_cast<const StreamCold *>(P.base + L.off_cold);
     return a;
 }
@@ -494,6 +545,7 @@ AdjStreamArgs adj_args(const Ptrs &P) {
     a.NX = d.NX; a.NY = d.NY; a.npml = d.npml; a.pitch = d.pitch;
     a.W = d.W; a.S = d.S; a.R = d.R; a.nt = d.nt;
     a.n_top = a.n_base = a.nlev = a.cur = 0;
+    a.group = L.depth;
     a.tl = tiling_adj(P);
     a.plane = d.plane; a.xs = d.xs; a.ys = d.ys;
     a.lev_stride = (size_t)d.S * d.plane;
@@ -506,6 +558,9 @@ AdjStreamArgs adj_args(const Ptrs &P) {
     a.E_lev = nullptr;
     a.L_in = a.LHx_in = a.LHy_in = nullptr;
     a.L_out = a.LHx_out = a.LHy_out = nullptr;
+    a.psi_in = a.psi_out = nullptr;
+    a.psi_y = align_up((size_t)d.S * d.ys * sizeof(float)) / sizeof(float);
+    a.psi_x = align_up((size_t)d.S * d.xs * sizeof(float)) / sizeof(float);
     a.S1 = L.off_S1 ? P.f(L.off_S1) : nullptr;
     a.S2 = L.off_S2 ? P.f(L.off_S2) : nullptr;
     a.cold = reinterpret_cast<const StreamCold *>(P.base + L.off_cold);
@@ -608,7 +663,7 @@ int setup(const Ptrs &P, const fwi_geom *g, const StreamCold &cold, const float 
     return FWI_OK;
 }
 
-// Forward steps [n0, n1) in passes of up to L.depth steps.  E of the pass
+// Forward steps [n0, n1) in passes of up to L.pass steps.  E of the pass
 // starting at n is read from ein(n); per-level E goes to elev(n) (history /
 // segment) or, when elev returns null, the final E of the pass to eout(n).
 // The H / CPML state ping-pongs between fwd[cur] and fwd[cur ^ 1].
@@ -619,9 +674,9 @@ int forward_passes(const Ptrs &P, FwdStreamArgs a, int n0, int n1, int &cur, EIn
     State fs[2] = {P.state(L.off_fwd[0], false), P.state(L.off_fwd[1], false)};
     a.record = record ? 1 : 0;
     const double all = (double)L.d.NX * L.d.NY * L.d.S;
-    for (int n = n0; n < n1; n += L.depth) {
+    for (int n = n0; n < n1; n += L.pass) {
         a.n = n;
-        a.nlev = std::min(L.depth, n1 - n);
+        a.nlev = std::min(L.pass, n1 - n);
         a.E_in = ein(n);
         a.E_lev = elev(n);
         a.E_out = a.E_lev ? nullptr : eout(n);
@@ -630,6 +685,8 @@ int forward_passes(const Ptrs &P, FwdStreamArgs a, int n0, int n1, int &cur, EIn
         a.Hy_in = fs[cur].Hy;
         a.Hx_out = fs[cur ^ 1].Hx;
         a.Hy_out = fs[cur ^ 1].Hy;
+        a.psi_in = fs[cur].phx;
+        a.psi_out = fs[cur ^ 1].phx;
         FWI_TRY(tm.run(a.E_lev ? K_FWD_REFWD : K_FWD_SWEEP, all * a.nlev,
                        [&] { return launch_fwd_stream(a, st); }));
         cur ^= 1;
@@ -713,7 +770,7 @@ int do_adjoint(const Layout &L, const float *eps_r, const float *sigma, float *g
     // every rounding, is the same for any checkpoint interval.
     auto adj_range = [&](int n_hi, int n_lo) -> int {
         for (int n_top = n_hi; n_top > n_lo; n_top -= a.nlev) {
-            a.nlev = n_top - std::max(n_lo, (n_top - 1) / L.depth * L.depth);
+            a.nlev = n_top - std::max(n_lo, (n_top - 1) / L.pass * L.pass);
             a.n_top = n_top;
             a.n_base = n_lo;
             a.E_lev = P.slot(0);
@@ -724,6 +781,8 @@ int do_adjoint(const Layout &L, const float *eps_r, const float *sigma, float *g
             a.L_out = as[acur ^ 1].E;
             a.LHx_out = as[acur ^ 1].Hx;
             a.LHy_out = as[acur ^ 1].Hy;
+            a.psi_in = as[acur].phx;
+            a.psi_out = as[acur ^ 1].phx;
             FWI_TRY(tm.run(K_ADJ, all * a.nlev, [&] { return launch_adj_stream(a, st); }));
             acur ^= 1;
         }

@@ -18,9 +18,17 @@ int make_dims(const fwi_grid *grid, const fwi_geom *geom, Dims &d);
 // Checkpoint interval minimising checkpoint plus segment-buffer memory.
 int stream_depth(const Dims &d);
 int choose_k(const Dims &d, int depth);
-// Row bands of the streaming decomposition (stored in L); `groups` shot
-// groups share the chip.
+// The decomposition of the stencil passes (stored in L): tiles or streams;
+// `groups` shot groups share the chip.
 void make_tiling(const Dims &d, Layout &L, int groups = 1);
+// Whether that many cells (all shots) run on tiles; a problem's tiles of the
+// large height; the height for that many tiles in flight; tiles of height
+// `rows` for both kernels; the streaming decomposition.
+bool use_tiles(long long cells);
+long long tile_count(const Dims &d);
+int pick_tile(long long tiles);
+void set_tiles(Layout &L, int rows);
+void set_streams(Layout &L, int groups = 1);
 // Row bands of height `rows` for both kernels (batched plans).
 void fixed_bands(Layout &L, int rows, int depth);
 // Workspace layout for a save mode (-1: fwi_gradient); k > 0 forces the

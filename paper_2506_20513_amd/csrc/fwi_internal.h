@@ -58,7 +58,10 @@ struct Layout {
     Dims d;
     int mode;          // FWI_SAVE_* or -1 for fwi_gradient
     int K;             // checkpoint interval (checkpoint modes)
-    int depth;         // temporal depth of the streaming passes
+    int depth;         // temporal depth of the streaming passes, and the steps
+                       // that the imaging sums group by
+    int pass;          // most levels per pass: depth, or kTileLevels with tiles
+    int tile;          // tile height of the tile kernels, 0: streaming kernels
     int ncp;           // number of checkpoints
     int nslots;        // Ez slots
     // streaming decomposition (see Tiling): row bands of the forward kernel
@@ -95,6 +98,12 @@ constexpr int kDepthSmall = 4;
 constexpr int kDepthLarge = 8;
 constexpr long long kDepthLargeCells = 1LL << 20;
 
+// Tile kernels (fwi_tile.hip): levels per pass and halo of a tile on every
+// side, and the tile heights (halo included) that are built.
+constexpr int kTileLevels = 8;
+constexpr int kTileRowsSmall = 32;
+constexpr int kTileRowsLarge = 64;
+
 // Source and receiver tables on the device.  Receivers of each shot are
 // sorted by (row, column), stable in receiver index; rrow is the row CSR.
 struct StreamGeom {
@@ -111,7 +120,9 @@ struct StreamGeom {
 struct Tiling {
     const int *bands;         // [nband + 1]
     int nstrip, nband;
-    int depth;                // temporal depth: kDepthSmall or kDepthLarge
+    int depth;                // most levels per pass: kDepthSmall or kDepthLarge
+                              // (streaming), kTileLevels (tiles)
+    int tile;                 // tile height of the tile kernels; 0: streaming
 };
 
 // Per-call constants of the stencil kernels that only rare branches read
@@ -143,6 +154,11 @@ struct FwdStreamArgs {
     float *E_lev;             // or null: Ez^{n+l+1} to E_lev + l * lev_stride
     const float *Hx_in, *Hy_in;
     float *Hx_out, *Hy_out;
+    // the CPML memories of the same states (their phx), and the padded sizes
+    // of their y-strip and x-strip arrays (tile kernels)
+    const float *psi_in;
+    float *psi_out;
+    size_t psi_y, psi_x;
     const StreamCold *cold;
 };
 
@@ -150,6 +166,7 @@ struct FwdStreamArgs {
 struct AdjStreamArgs {
     int NX, NY, npml, pitch, W, S, R, nt;
     int n_top, n_base, nlev;
+    int group;                // the imaging sums group by this many steps (tiles)
     int cur;                  // input state cold->as[cur], output as[cur ^ 1]
     Tiling tl;
     size_t plane, xs, ys, lev_stride;
@@ -158,6 +175,9 @@ struct AdjStreamArgs {
     const float *E_lev;       // forward Ez^{n_base + k} at E_lev + k * lev_stride
     const float *L_in, *LHx_in, *LHy_in;
     float *L_out, *LHx_out, *LHy_out;
+    const float *psi_in;      // as in FwdStreamArgs
+    float *psi_out;
+    size_t psi_y, psi_x;
     float *S1, *S2;           // per-shot correlation sums [S][NY][pitch]
     const StreamCold *cold;
 };
@@ -195,20 +215,29 @@ hipError_t launch_residual_misfit(const float *traces, const float *observed,
 hipError_t launch_finite_check(const float *a, size_t na, const float *b, size_t nb,
                                const double *scalar, double *partials, int *flag,
                                hipStream_t st);
-// streaming kernels (fwi_stream.hip)
+// stencil passes: the streaming kernels (fwi_stream.hip) or, where a.tl.tile
+// is set, the tile kernels (fwi_tile.hip)
 hipError_t launch_fwd_stream(const FwdStreamArgs &a, hipStream_t st);
 hipError_t launch_adj_stream(const AdjStreamArgs &a, hipStream_t st);
 // Blocks one problem's pass launches.
 unsigned stream_blocks(int S, const Tiling &tl);
 // One pass for nm problems at once: tab[m] (device) holds problem m's
 // arguments and boff[0..nm] (device) the prefix sums of their block counts,
-// nblocks = boff[nm].  depth: the passes' temporal depth (kDepthSmall or
-// kDepthLarge, the same for every problem of the launch); tail: the
-// problems advance fewer than depth levels.  lev (forward only): 1 if every
+// nblocks = boff[nm].  depth: table_depth of the passes' tiling, the same for
+// every problem of the launch; tail (streaming): the problems advance fewer
+// than depth levels.  lev (forward only): 1 if every
 // problem's entry has E_lev set (segment re-forward), 0 if none has.
+inline int table_depth(const Tiling &tl) { return tl.depth | tl.tile << 8; }
 hipError_t launch_fwd_table(const FwdStreamArgs *tab, const unsigned *boff, int nm,
                             unsigned nblocks, int depth, bool tail, int lev, hipStream_t st);
 hipError_t launch_adj_table(const AdjStreamArgs *tab, const unsigned *boff, int nm,
                             unsigned nblocks, int depth, bool tail, hipStream_t st);
+// the tile kernels behind them
+hipError_t launch_fwd_tile(const FwdStreamArgs &a, hipStream_t st);
+hipError_t launch_adj_tile(const AdjStreamArgs &a, hipStream_t st);
+hipError_t launch_fwd_tile_table(const FwdStreamArgs *tab, const unsigned *boff, int nm,
+                                 unsigned nblocks, int rows, int lev, hipStream_t st);
+hipError_t launch_adj_tile_table(const AdjStreamArgs *tab, const unsigned *boff, int nm,
+                                 unsigned nblocks, int rows, hipStream_t st);
 
 }  // namespace fwi

@@ -35,7 +35,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # the kernels, and the host code that picks their launch decomposition
-KERNEL_SOURCES = ("csrc/fwi_stream.hip", "csrc/fwi_internal.h", "csrc/fwi_host.cpp")
+KERNEL_SOURCES = ("csrc/fwi_stream.hip", "csrc/fwi_tile.hip", "csrc/fwi_stencil.h",
+                  "csrc/fwi_internal.h", "csrc/fwi_host.cpp")
 STENCIL = ("k_fwd_sweep", "k_fwd_reforward", "k_adj")
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
