@@ -12,12 +12,17 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
 #include "fwi_nn.h"
 
 namespace {
 
 using bf16 = __bf16;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -263,6 +268,204 @@ __global__ __launch_bounds__(256) void k_conv3x3_lds(const bf16 *__restrict__ x,
     }
 }
 
+// The same convolution for 32, 64 and 128 input channels, marching down the rows
+// of a strip of at most 4096 / CI pixels of one image.  Each wave keeps the weights of its 16
+// CT output channels for all nine taps and all input channels in registers
+// (9 CI / 32 CT fragments); the input rows pass once through a ring of four
+// rows in LDS, one pixel of halo on both sides and zeros outside the image, so
+// a fragment needs no mask.  Per output row one row is loaded (in flight while
+// the row before it is computed) and one barrier passed.  The four waves are CG
+// groups of channels x PG groups of 16-pixel tiles.  The weights are the row
+// operand of the products, so a lane holds four neighbouring channels of one
+// pixel and stores them as 8 bytes.  KXC: the reduction runs over (ky, kx, ci)
+// instead of (ky, ci / 32, kx): the order of the kernel that serves the same
+// layer otherwise, so every sum is the same bit for bit.
+//
+// 32 channels are bound by memory (1024 x 2048 pixels: 120 -> 50 us, 5.4 TB/s;
+// 32 images of 128 x 128: 39 -> 18 us), 64 and 128 channels by the fragment reads
+// from LDS, one kilobyte for CT products (512 x 1024 pixels, 64 channels: 81 -> 43
+// us, 0.9 PFLOP/s; 256 x 512, 128 channels: 71 -> 50 us); the network's training
+// layers of 64 and 128 channels by the start of a block, about 11 us (32 images
+// of 64 x 64, 64 channels: 28.6 -> 20.7 us).  256 channels would need 288
+// registers of weights per lane: one wave per SIMD, slower (70 -> 91 us).
+template <int CI, int CT, int CG, int PG, bool KXC>
+__global__ __launch_bounds__(256) void k_conv3x3_rows(const bf16 *__restrict__ x,
+                                                      const bf16 *__restrict__ w,
+                                                      const float *__restrict__ bias,
+                                                      bf16 *__restrict__ y, int H, int W, int Co,
+                                                      int relu, int strip, int nstrip, int rows,
+                                                      int nrow) {
+    static_assert(CG * PG == 4, "four waves");
+    constexpr int NC = CI / 32, PITCH = CI + 8, BW = 4096 / CI, PT = (BW / 16 + PG - 1) / PG;
+    constexpr int RowPieces = (BW + 2) * CI / 8, U = (RowPieces + 255) / 256;
+    __shared__ __attribute__((aligned(16))) bf16 ring[4][(BW + 2) * PITCH];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int cg = wave % CG, pg = wave / CG, kq = 8 * (lane >> 4);
+    // block -> (image, band of rows, strip); strips fastest
+    const int sx = blockIdx.x % nstrip, by = blockIdx.x / nstrip;
+    const int n = by / nrow, y0 = by % nrow * rows, y1 = min(H, y0 + rows);
+    const int xs = sx * strip, sw = min(strip, W - xs);
+    const int co0 = (blockIdx.y * CG + cg) * 16 * CT;
+    const bf16 *xi = x + (size_t)n * H * W * CI;
+
+    uint4 pre[U];
+    const int pieces = (sw + 2) * (CI / 8);
+    auto fetch = [&](int yy, uint4 *pre) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int idx = t + 256 * u, j = idx / (CI / 8), c = idx % (CI / 8) * 8;
+            const int xx = xs - 1 + j;
+            pre[u] = make_uint4(0u, 0u, 0u, 0u);
+            if (idx < pieces && yy >= 0 && yy < H && xx >= 0 && xx < W)
+                pre[u] = *reinterpret_cast<const uint4 *>(xi + ((size_t)yy * W + xx) * CI + c);
+        }
+    };
+    auto stash = [&](int slot, const uint4 *pre) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int idx = t + 256 * u, j = idx / (CI / 8), c = idx % (CI / 8) * 8;
+            if (idx < pieces) *reinterpret_cast<uint4 *>(&ring[slot][j * PITCH + c]) = pre[u];
+        }
+    };
+    uint4 first[3][U];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) fetch(y0 - 1 + k, first[k]);
+    bf16x8 wf[3][NC][3][CT];
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+                    wf[ky][c][kx][ct] = *reinterpret_cast<const bf16x8 *>(
+                        w + ((size_t)(co0 + 16 * ct + (lane & 15)) * 9 + ky * 3 + kx) * CI +
+                        32 * c + kq);
+    float bb[CT][4];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            bb[ct][r] = bias ? bias[co0 + 16 * ct + 4 * (lane >> 4) + r] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) stash(k, first[k]);
+
+    for (int yo = y0; yo < y1; ++yo) {
+        const int k0 = yo - y0;
+        __syncthreads();
+        if (yo + 1 < y1) fetch(yo + 2, pre);
+        // NP tiles of 16 pixels from tile pt0 on, together
+        auto tiles = [&](auto np, int pt0) {
+            constexpr int NP = decltype(np)::value;
+            f32x4 acc[NP][CT];
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int p0 = (pg * PT + pt0) * 16 + (lane & 15);
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) {
+                const bf16 *row = &ring[(k0 + ky) & 3][p0 * PITCH + kq];
+                auto tap = [&](int c, int kx) {
+#pragma unroll
+                    for (int i = 0; i < NP; ++i) {
+                        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(
+                            row + (16 * i + kx) * PITCH + 32 * c);
+#pragma unroll
+                        for (int ct = 0; ct < CT; ++ct)
+                            acc[i][ct] = mfma(wf[ky][c][kx][ct], a, acc[i][ct]);
+                    }
+                };
+                if (KXC) {
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) tap(c, kx);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int kx = 0; kx < 3; ++kx) tap(c, kx);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int p = p0 + 16 * i;
+                if (p >= sw) continue;
+                bf16 *out = y + (((size_t)n * H + yo) * W + xs + p) * Co + co0 + 4 * (lane >> 4);
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    bf16x4 v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float f = acc[i][ct][r] + bb[ct][r];
+                        if (relu) f = fmaxf(f, 0.f);
+                        v[r] = (bf16)f;
+                    }
+                    *reinterpret_cast<bf16x4 *>(out + 16 * ct) = v;
+                }
+            }
+        };
+        // this wave's tiles, two at a time
+        const int nt = min(PT, (sw - pg * PT * 16 + 15) / 16);
+        int pt = 0;
+        if (PT > 1)
+            for (; pt + 1 < nt; pt += 2) tiles(std::integral_constant<int, (PT > 1 ? 2 : 1)>(), pt);
+        if (pt < nt) tiles(std::integral_constant<int, 1>(), pt);
+        if (yo + 1 < y1) stash((k0 + 3) & 3, pre);
+    }
+}
+
+// Bands of rows per image for `base` strips and channel groups: a block pays
+// about 6 rows' time for its weights and first rows and reads 2 halo rows; with
+// one block per CU nothing hides its latencies (weighed 1.3), two share a CU, and
+// of a last, partial round beyond that half the idle time counts.  Fitted to
+// sweeps of the block count over the network's layers: 32 images of 128 x 128,
+// 32 channels, best at 512 blocks (18.6 us; 256: 22.4, 1024: 20.8), of 32 x 32,
+// 64 to 128 channels, at 256 (13.2; 512: 14.8, 1024: 20.8).
+int row_bands(long long base, int H) {
+    int best = 1;
+    double best_t = 1e300;
+    for (int nb = 1; nb <= H && (nb == 1 || base * nb <= 4096); ++nb) {
+        const int rows = (H + nb - 1) / nb;
+        const double r = (double)(base * nb) / 256.0, up = std::ceil(r);
+        const double rounds = r <= 1.0 ? 1.3 : (r <= 2.0 ? up : r + 0.5 * (up - r));
+        const double t = (rows + 2) * rounds + 6.0 * std::ceil(r / 2.0);
+        if (t < best_t) {
+            best_t = t;
+            best = nb;
+        }
+    }
+    return best;
+}
+
+// Share of the 16-pixel tiles of an image row that is image, in strips of at most
+// bw pixels.
+double row_use(int W, int bw) {
+    const int nstrip = (W + bw - 1) / bw, strip = (W + nstrip - 1) / nstrip;
+    return (double)W / (nstrip * ((strip + 15) / 16 * 16));
+}
+
+template <int CI, int CT, int CG, int PG>
+hipError_t launch_rows(const bf16 *x, const bf16 *w, const float *bias, bf16 *y, int N, int H,
+                       int W, int Co, int relu, bool kxc, hipStream_t st) {
+    constexpr int BW = 4096 / CI;
+    const int nstrip = (W + BW - 1) / BW, strip = (W + nstrip - 1) / nstrip;
+    const int nco = Co / (16 * CT * CG);
+    const int bands = row_bands((long long)N * nstrip * nco, H);
+    const int rows = (H + bands - 1) / bands, nrow = (H + rows - 1) / rows;
+    const dim3 grid((unsigned)(N * nrow * nstrip), (unsigned)nco);
+    if (kxc)
+        hipLaunchKernelGGL((k_conv3x3_rows<CI, CT, CG, PG, true>), grid, dim3(256), 0, st, x, w,
+                           bias, y, H, W, Co, relu, strip, nstrip, rows, nrow);
+    else
+        hipLaunchKernelGGL((k_conv3x3_rows<CI, CT, CG, PG, false>), grid, dim3(256), 0, st, x, w,
+                           bias, y, H, W, Co, relu, strip, nstrip, rows, nrow);
+    return hipGetLastError();
+}
+
 // wf[ci][ky][kx][co] = w[co][2-ky][2-kx][ci]: the weights of the transposed
 // convolution (input gradient = conv3x3(output gradient, wf)).
 __global__ void k_flip(const bf16 *__restrict__ w, bf16 *__restrict__ wf, int Ci, int Co) {
@@ -328,7 +531,6 @@ __global__ void k_flip_layers(const bf16 *__restrict__ w, bf16 *__restrict__ wf,
 constexpr int kWP = 40;     // LDS row pitch in bf16: 32 channels + 8 padding
 constexpr int kWgradChunk = 32;   // pixels staged per step of k_wgrad
 
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((address_space(3))) bf16x4 *lds_bf16x4_ptr;
 
 // channels [16 h, 16 h + 16) of rows base .. base + 7 of a pixel-major LDS
@@ -870,6 +1072,31 @@ int fwi_nn_conv3x3(const void *x, const void *w, const float *bias, void *y, int
     int bn = Co % 64 == 0 ? 64 : 32;
     if (bn == 64 && (P + 127) / 128 * (Co / 64) < 256) bn = 32;
     const int64_t lds_blocks = (P + 127) / 128 * (Co / bn);
+    // Row-marching kernel for 32, 64 and 128 input channels where y allows its
+    // 8-byte stores: always in place of the smallest layers' kernel (128 -> 64
+    // channels, 3 images of 45 x 83: 26.6 -> 9.5 us), and in place of the
+    // LDS-tiled one unless its 16-pixel tiles pad the rows too much (20 images
+    // of 100 x 17, 128 channels: 26.8 -> 31.5 us, of 144 columns 30.2 -> 32.0;
+    // 32 of 70 x 18, 64 channels: 12.9 -> 18.3) or there is too little to win
+    // against its start (64 -> 32 channels, 32 images of 18 x 130: 12.8 -> 14.3)
+    const bool kxc = lds_blocks < 256;
+    if ((Ci <= 64 || Ci == 128) && (reinterpret_cast<uintptr_t>(y) & 7) == 0 &&
+        (kxc || (row_use(W, 4096 / Ci) >= (Ci == 128 ? 0.92 : 0.8) &&
+                 !(Ci == 64 && Co == 32 && P < 1 << 17)))) {
+        hipError_t e;
+        if (Ci == 32)
+            e = Co % 64 == 0 ? launch_rows<32, 2, 2, 2>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st)
+                             : launch_rows<32, 2, 1, 4>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+        else if (Ci == 128)
+            e = Co % 64 == 0 ? launch_rows<128, 1, 4, 1>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st)
+                             : launch_rows<128, 1, 2, 2>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+        else if (Co % 128 == 0)
+            e = launch_rows<64, 2, 4, 1>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+        else
+            e = Co % 64 == 0 ? launch_rows<64, 2, 2, 2>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st)
+                             : launch_rows<64, 2, 1, 4>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+        return status(e);
+    }
     if (lds_blocks >= 256) {
         // (the 64-pixel tile below 1024 blocks of 128 made the network's
         // 32 x 32-pixel layers slower)
