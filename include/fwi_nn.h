@@ -65,8 +65,8 @@ int fwi_nn_flip_layers(const void *w, void *wf, int32_t nlayers, const int64_t *
 /* Weight and bias gradients of y = conv3x3(x, w) + b given dz = dL/dy:
  *   dw[co][ky][kx][ci] = sum over pixels p of dz[p][co] x[p + (ky-1, kx-1)][ci],
  *   db[co] = sum_p dz[p][co]   (float32 outputs, overwritten).
- * The pixel sum is split over nsplit partial sums reduced in a fixed order,
- * so results are deterministic.  x and dz 16-byte aligned, N * H * W < 2^36,
+ * The pixel sum is split over at most nsplit partial sums reduced in a fixed
+ * order, so results are deterministic.  x and dz 16-byte aligned, N * H * W < 2^36,
  * H, W <= 32768, 1 <= nsplit <= 65535.  ws: device scratch of at least
  * fwi_nn_wgrad_workspace(Ci, Co, nsplit) bytes, 4-byte aligned. */
 size_t fwi_nn_wgrad_workspace(int32_t Ci, int32_t Co, int32_t nsplit);

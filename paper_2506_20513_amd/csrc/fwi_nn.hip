@@ -677,6 +677,282 @@ __global__ __launch_bounds__(256) void k_wgrad(const bf16 *__restrict__ x,
     if (do_bias && t < 32) o[tile + cot * 32 + t] = bsum;
 }
 
+// The same gradients for images of 128 pixels and more, marching down the rows of strips of at most BW pixels as
+// the row convolution does: input rows pass once through a ring in LDS (one
+// pixel of halo, zeros outside the image), output-gradient rows through another.
+// A block owns 32 x 32 channels for all nine taps; each of its NW waves keeps all
+// of them (36 sums of 16 x 16 in registers), so a fragment read from LDS serves
+// several products, and the waves take turns at the pixels.  The reduction index
+// of a product is 32 pixels: four groups of 8 neighbouring pixels of a row, which
+// may lie in different rows, so narrow images keep the matrix cores as busy as
+// wide ones (rows are padded to 8 pixels with zero gradients).  A lane reads 12
+// pixels of one channel by three transposing reads and shifts the fragments of
+// the three kx taps out of them.  Block b takes the steps (strips of the images,
+// srow rows at a time) [b T / G, (b + 1) T / G) and writes one record of sums.
+// The accumulators leave two waves per SIMD, so a step's loads (issued one step
+// ahead) are what it waits for, about 1.8 us for 0.6 us of products and LDS reads;
+// loads two steps ahead, or half the sums per wave and four waves, spill registers
+// (41 and 54 us against 31 for 32 x 128 x 128 pixels, 32 -> 32 channels).
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // records: 4-byte aligned
+constexpr int kWRP = 40;    // pitch of a pixel in LDS: 32 channels + 8 padding
+
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_wgrad_rows(
+    const bf16 *__restrict__ x, const bf16 *__restrict__ dz, float *__restrict__ part, int N,
+    int H, int W, int Ci, int Co, int strip, int nstrip, int srow) {
+    constexpr int BW = 32 * NW, NT = 64 * NW, P = kWRP;
+    // 16-byte pieces per thread of srow rows: at most BW pixels of Z; of X two
+    // pixels of halo more per row, of at most BW / 8 rows
+    constexpr int UX = (BW * 5 + NT - 1) / NT, UZ = BW * 4 / NT;
+    // X ring: 2 srow + 2 rows of strip8 + 4 pixels, at most 4 (BW + 4) pixels as
+    // srow strip8 <= BW and strip8 >= 8; Z: 2 srow rows of strip8 pixels; pixels
+    // of zeros behind each
+    constexpr int XAll = 4 * (BW + 4) + 12, ZAll = 2 * BW + 8;
+    __shared__ __attribute__((aligned(16))) bf16 Xs[XAll * P];
+    __shared__ __attribute__((aligned(16))) bf16 Zs[ZAll * P];
+    const int t = threadIdx.x, lane = t & 63, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int nci = Ci / 32, cit = blockIdx.y % nci * 32, cot = blockIdx.y / nci * 32;
+    const int strip8 = (strip + 7) / 8 * 8, G8 = strip8 / 8, xrow = strip8 + 4;
+    const int nx = 2 * srow + 2, nz = 2 * srow;              // ring sizes in rows
+    const int xzero = nx * xrow, zzero = nz * strip8;        // pixel index of the zeros behind
+    // this thread's pieces of srow rows: row and pixel
+    const SmallDiv dX((unsigned)(strip + 2)), dZ((unsigned)strip), dG((unsigned)G8);
+    int xr[UX], xj[UX], zr[UZ], zj[UZ];
+#pragma unroll
+    for (int u = 0; u < UX; ++u) {
+        const unsigned q = (unsigned)(t + NT * u) >> 2;
+        xr[u] = (int)dX.div(q);
+        xj[u] = (int)dX.mod(q);
+    }
+#pragma unroll
+    for (int u = 0; u < UZ; ++u) {
+        const unsigned q = (unsigned)(t + NT * u) >> 2;
+        zr[u] = (int)dZ.div(q);
+        zj[u] = (int)dZ.mod(q);
+    }
+    const int c8 = (t & 3) * 8;
+    const int per = (H + srow - 1) / srow;                   // steps of a strip
+    const long long T = (long long)N * nstrip * per;
+    const long long s0 = T * blockIdx.x / gridDim.x, s1 = T * (blockIdx.x + 1) / gridDim.x;
+
+    int sw = 0, xs = 0;                                      // the strip's width and first column
+    const bf16 *xi = x, *zi = dz;
+    // nr rows of X from row yy on; srow rows of Z
+    auto fetch_x = [&](uint4 (&px)[UX], int yy, int nr) {
+#pragma unroll
+        for (int u = 0; u < UX; ++u) {
+            px[u] = make_uint4(0u, 0u, 0u, 0u);
+            const int y = yy + xr[u], xx = xs - 1 + xj[u];
+            if (xr[u] < nr && y >= 0 && y < H && xx >= 0 && xx < W && xj[u] < sw + 2)
+                px[u] = *reinterpret_cast<const uint4 *>(xi + ((size_t)y * W + xx) * Ci + cit + c8);
+        }
+    };
+    auto fetch_z = [&](uint4 (&pz)[UZ], int yy) {
+#pragma unroll
+        for (int u = 0; u < UZ; ++u) {
+            pz[u] = make_uint4(0u, 0u, 0u, 0u);
+            const int y = yy + zr[u];
+            if (zr[u] < srow && y < H && zj[u] < sw)
+                pz[u] = *reinterpret_cast<const uint4 *>(zi + ((size_t)y * W + xs + zj[u]) * Co +
+                                                         cot + c8);
+        }
+    };
+    auto stash_x = [&](const uint4 (&px)[UX], int slot, int nr) {   // slot of the first row
+#pragma unroll
+        for (int u = 0; u < UX; ++u) {
+            int r = slot + xr[u];
+            if (r >= nx) r -= nx;
+            if (xr[u] < nr) *reinterpret_cast<uint4 *>(&Xs[(r * xrow + xj[u]) * P + c8]) = px[u];
+        }
+    };
+    auto stash_z = [&](const uint4 (&pz)[UZ], int slot) {
+#pragma unroll
+        for (int u = 0; u < UZ; ++u)
+            if (zr[u] < srow)
+                *reinterpret_cast<uint4 *>(&Zs[((slot + zr[u]) * strip8 + zj[u]) * P + c8]) = pz[u];
+    };
+    f32x4 acc[2][2][9], bacc[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        bacc[o] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) acc[o][i][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.f;
+    const bool do_bias = cit == 0;
+    // transposing read of pixels p .. p + 3, channels ch .. ch + 15
+    const int lo = ((lane & 15) >> 2) * P + 4 * (lane & 3);
+    auto tr = [&](const bf16 *tile, int p, int ch) {
+        return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                                             (lds_bf16x4_ptr)(tile + p * P + ch + lo)));
+    };
+
+    int xb = 0, zb = 0;                                      // slots of row y - 1 of X, y of Z
+    int y = 0;
+    const int chunks = (srow * G8 + 3) / 4;
+    for (long long st = s0; st < s1; ++st) {
+        if (st == s0 || y >= H) {                            // a new strip
+            const long long col = st / per;
+            y = (int)(st - col * per) * srow;
+            const long long n = col / nstrip;
+            xs = (int)(col - n * nstrip) * strip;
+            sw = min(strip, W - xs);
+            xi = x + n * H * W * Ci;
+            zi = dz + n * H * W * Co;
+            xb = zb = 0;
+            // rows y - 1 .. y + srow of X, all in flight together
+            uint4 p0[UX], p1[UX], p2[UX], pz[UZ];
+            const int more = min(srow, 2);
+            fetch_x(p0, y - 1, srow);
+            fetch_x(p1, y - 1 + srow, more);
+            if (more == 1) fetch_x(p2, y + srow, 1);
+            fetch_z(pz, y);
+            if (st == s0) {
+                // the padding pixels stay zero from here on
+                for (int i = t; i < XAll * P / 8; i += NT)
+                    reinterpret_cast<uint4 *>(Xs)[i] = make_uint4(0u, 0u, 0u, 0u);
+                for (int i = t; i < ZAll * P / 8; i += NT)
+                    reinterpret_cast<uint4 *>(Zs)[i] = make_uint4(0u, 0u, 0u, 0u);
+            }
+            __syncthreads();
+            stash_x(p0, 0, srow);
+            stash_x(p1, srow, more);
+            if (more == 1) stash_x(p2, 2, 1);
+            stash_z(pz, 0);
+        }
+        __syncthreads();
+        const bool next = st + 1 < s1 && y + srow < H;
+        uint4 px[UX], pz[UZ];
+        if (next) {
+            fetch_x(px, y + srow + 1, srow);
+            fetch_z(pz, y + srow);
+        }
+        for (int c = wave; c < chunks; c += NW) {
+            const int gi = 4 * c + g;
+            const int r = (int)dG.div((unsigned)gi), p8 = 8 * (gi - r * G8);
+            const bool in = r < srow && y + r < H;
+            const int zp = in ? (zb + r) * strip8 + p8 : zzero;
+            bf16x8 a[2];
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                const uint2 d0 = tr(Zs, zp, 16 * o), d1 = tr(Zs, zp + 4, 16 * o);
+                a[o] = __builtin_bit_cast(bf16x8, make_uint4(d0.x, d0.y, d1.x, d1.y));
+                if (do_bias) bacc[o] = mfma(a[o], ones, bacc[o]);
+            }
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky) {
+                int q = xb + r + ky;
+                if (q >= nx) q -= nx;
+                const int xp = in ? q * xrow + p8 : xzero;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint2 d0 = tr(Xs, xp, 16 * i), d1 = tr(Xs, xp + 4, 16 * i),
+                                d2 = tr(Xs, xp + 8, 16 * i);
+                    const bf16x8 b0 =
+                        __builtin_bit_cast(bf16x8, make_uint4(d0.x, d0.y, d1.x, d1.y));
+                    const bf16x8 b1 = __builtin_bit_cast(
+                        bf16x8, make_uint4(__builtin_amdgcn_alignbit(d0.y, d0.x, 16),
+                                           __builtin_amdgcn_alignbit(d1.x, d0.y, 16),
+                                           __builtin_amdgcn_alignbit(d1.y, d1.x, 16),
+                                           __builtin_amdgcn_alignbit(d2.x, d1.y, 16)));
+                    const bf16x8 b2 =
+                        __builtin_bit_cast(bf16x8, make_uint4(d0.y, d1.x, d1.y, d2.x));
+#pragma unroll
+                    for (int o = 0; o < 2; ++o) {
+                        acc[o][i][3 * ky] = mfma(b0, a[o], acc[o][i][3 * ky]);
+                        acc[o][i][3 * ky + 1] = mfma(b1, a[o], acc[o][i][3 * ky + 1]);
+                        acc[o][i][3 * ky + 2] = mfma(b2, a[o], acc[o][i][3 * ky + 2]);
+                    }
+                }
+            }
+        }
+        if (next) {
+            int xn = xb + srow + 2;                          // slot of row y + srow + 1
+            if (xn >= nx) xn -= nx;
+            zb = zb ? 0 : srow;
+            stash_x(px, xn, srow);
+            stash_z(pz, zb);
+            xb += srow;
+            if (xb >= nx) xb -= nx;
+        }
+        y += srow;
+    }
+    // the waves' sums in wave order: the waves take the 16 x 16 tiles of two taps
+    // in turns.  A lane holds four input channels of one output channel and
+    // stores them at once.
+    const size_t tile = (size_t)Co * 9 * Ci;
+    float *out = part + blockIdx.x * (tile + Co);
+    float *red = reinterpret_cast<float *>(Xs);              // [wave][tap][tile][256]
+    static_assert(sizeof(Xs) >= NW * 8 * 256 * sizeof(float), "two taps' tiles fit");
+#pragma unroll
+    for (int k0 = 0; k0 < 9; k0 += 2) {
+        const int nk = k0 + 2 <= 9 ? 2 : 1;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < nk; ++k)
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                *reinterpret_cast<f32x4 *>(&red[((wave * 2 + k) * 4 + m) * 256 + 4 * lane]) =
+                    acc[m >> 1][m & 1][k0 + k];
+        __syncthreads();
+#pragma unroll
+        for (int q = wave; q < nk * 4; q += NW) {
+            f32x4 v = *reinterpret_cast<const f32x4 *>(&red[q * 256 + 4 * lane]);
+#pragma unroll
+            for (int w2 = 1; w2 < NW; ++w2)
+                v += *reinterpret_cast<const f32x4 *>(&red[(w2 * 8 + q) * 256 + 4 * lane]);
+            const int co = cot + 16 * (q >> 1 & 1) + (lane & 15);
+            const int ci = cit + 16 * (q & 1) + 4 * g;
+            *reinterpret_cast<f32x4_a4 *>(&out[((size_t)co * 9 + k0 + (q >> 2)) * Ci + ci]) = v;
+        }
+    }
+    if (!do_bias) return;
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+        if ((lane & 15) == 0)
+            *reinterpret_cast<f32x4 *>(&red[wave * 32 + 16 * o + 4 * g]) = bacc[o];
+    __syncthreads();
+    if (t < 32) {
+        float v = red[t];
+#pragma unroll
+        for (int w2 = 1; w2 < NW; ++w2) v += red[w2 * 32 + t];
+        out[tile + cot + t] = v;
+    }
+}
+
+// Strips and rows per step of k_wgrad_rows: the pair with the fewest steps (of
+// at most BW pixels each), the widest strips among equals (least halo).
+struct WgradPlan {
+    int strip, nstrip, srow;
+    long long steps;
+};
+
+template <int BW>
+WgradPlan wgrad_plan(int N, int H, int W) {
+    WgradPlan best{};
+    const int least = (W + BW - 1) / BW;
+    for (int n = least; n <= least + 8; ++n) {
+        const int strip = n == 1 ? W : ((W + n - 1) / n + 7) / 8 * 8;
+        const int strip8 = (strip + 7) / 8 * 8;
+        const int ns = (W + strip - 1) / strip, srow = std::min(BW / strip8, H);
+        const long long steps = (long long)N * ns * ((H + srow - 1) / srow);
+        if (best.steps == 0 || steps < best.steps) best = {strip, ns, srow, steps};
+        if (strip8 <= 16) break;
+    }
+    return best;
+}
+
+// records of sums: at most `nsplit`, one per step, and `fill` blocks
+int wgrad_blocks(int nsplit, long long steps, int fill) {
+    return (int)std::min<long long>({(long long)nsplit, steps, (long long)std::max(1, fill)});
+}
+
 // sum_k part[k][i] over the nsplit records of n = n1 + n2 floats, written
 // to out1[i] for i < n1 and to out2[i - n1] after: 64 outputs per block, GR
 // groups of waves summing the splits k = g (mod GR) with four loads in
@@ -1168,9 +1444,34 @@ int fwi_nn_wgrad(const void *x, const void *dz, float *dw, float *db, int32_t N,
         return FWI_NN_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     float *part = static_cast<float *>(ws);
-    hipLaunchKernelGGL(k_wgrad<kWgradChunk>, dim3(nsplit, (Co / 32) * (Ci / 32)), dim3(256), 0, st,
-                       static_cast<const bf16 *>(x), static_cast<const bf16 *>(dz), part, N, H, W,
-                       Ci, Co);
+    const int tiles = (Co / 32) * (Ci / 32);
+    // As many blocks as the chip holds at once, one of eight waves per CU or two
+    // of four.  Eight waves write half the records: with up to 8 steps per block
+    // (3 x 45 x 83, 64 -> 128: 17.9 us against 22.1 with four; 32 x 128 x 128, 32
+    // channels: 30.3, 31.7).  Beyond, two blocks that wait for each other's loads
+    // (1024 x 2048, 32 channels: 83.7 against 79.0; 512 x 1024, 64: 76.2, 68.2).
+    // Images below 128 pixels leave a step's pixels mostly padding and start a
+    // strip each step: the flattened form (512 x 8 x 8, 128 channels: 44.6 us
+    // against 47.2; 1024 x 1 x 1, 64 channels: 12.8, 64.1); from 32 x 13 x 14 on,
+    // 64 -> 32 channels, the rows win (12.6 against 14.7; 32 x 16 x 16, 256
+    // channels: 33.3, 44.4).
+    const WgradPlan p8 = wgrad_plan<256>(N, H, W), p4 = wgrad_plan<128>(N, H, W);
+    const int g8 = wgrad_blocks(nsplit, p8.steps, 256 / tiles);
+    if (H * W < 128) {
+        hipLaunchKernelGGL(k_wgrad<kWgradChunk>, dim3(nsplit, tiles), dim3(256), 0, st,
+                           static_cast<const bf16 *>(x), static_cast<const bf16 *>(dz), part, N, H,
+                           W, Ci, Co);
+    } else if (p8.steps <= 8LL * g8) {
+        nsplit = g8;
+        hipLaunchKernelGGL(k_wgrad_rows<8>, dim3(nsplit, tiles), dim3(512), 0, st,
+                           static_cast<const bf16 *>(x), static_cast<const bf16 *>(dz), part, N, H,
+                           W, Ci, Co, p8.strip, p8.nstrip, p8.srow);
+    } else {
+        nsplit = wgrad_blocks(nsplit, p4.steps, 512 / tiles);
+        hipLaunchKernelGGL(k_wgrad_rows<4>, dim3(nsplit, tiles), dim3(256), 0, st,
+                           static_cast<const bf16 *>(x), static_cast<const bf16 *>(dz), part, N, H,
+                           W, Ci, Co, p4.strip, p4.nstrip, p4.srow);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return FWI_NN_EHIP;
     const size_t nw = (size_t)Co * 9 * Ci, n = nw + Co;
