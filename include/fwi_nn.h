@@ -49,6 +49,12 @@ extern "C" {
  * output gradient with the weights from fwi_nn_flip (Ci and Co swapped). */
 int fwi_nn_conv3x3(const void *x, const void *w, const float *bias, void *y, int32_t N,
                    int32_t H, int32_t W, int32_t Ci, int32_t Co, int32_t relu, void *stream);
+/* The same without bias and activation, zero where mask [N][H][W][Co] bf16 is
+ * not positive (must not alias y): an input gradient and the adjoint
+ * of the ReLU before it in one pass, the same values as fwi_nn_conv3x3 followed
+ * by fwi_nn_relu_bwd. */
+int fwi_nn_conv3x3_masked(const void *x, const void *w, const void *mask, void *y, int32_t N,
+                          int32_t H, int32_t W, int32_t Ci, int32_t Co, void *stream);
 
 /* wf[ci][2-ky][2-kx][co] = w[co][ky][kx][ci]: w [Co][3][3][Ci] -> wf
  * [Ci][3][3][Co], the weights of the transposed convolution. */
@@ -88,6 +94,9 @@ int fwi_nn_pool2_bwd(const void *dy, void *dx, int32_t N, int32_t H, int32_t W, 
  * fwi_nn_pool2_bwd followed by fwi_nn_add. */
 int fwi_nn_pool2_bwd_add(const void *dy, const void *skip, void *dx, int32_t N, int32_t H,
                          int32_t W, int32_t C, void *stream);
+/* The same, zero where mask [N][H][W][C] is not positive (must not alias dx). */
+int fwi_nn_pool2_bwd_masked(const void *dy, const void *skip, const void *mask, void *dx,
+                            int32_t N, int32_t H, int32_t W, int32_t C, void *stream);
 
 /* y [N][Ho][Wo][C] = nearest 2x upsampling of x [N][Ho/2][Wo/2][C] plus
  * skip [N][Ho][Wo][C] (NULL = no skip); fwi_nn_up2_bwd is the adjoint of
@@ -97,6 +106,9 @@ int fwi_nn_up2_add(const void *x, const void *skip, void *y, int32_t N, int32_t 
                    int32_t C, void *stream);
 int fwi_nn_up2_bwd(const void *dy, void *dx, int32_t N, int32_t Hi, int32_t Wi, int32_t C,
                    void *stream);
+/* The same, zero where mask [N][Hi][Wi][C] is not positive (must not alias dx). */
+int fwi_nn_up2_bwd_masked(const void *dy, const void *mask, void *dx, int32_t N, int32_t Hi,
+                          int32_t Wi, int32_t C, void *stream);
 
 /* y[i] = a[i] + b[i] over n bf16 values (y may alias a or b). */
 int fwi_nn_add(const void *a, const void *b, void *y, size_t n, void *stream);

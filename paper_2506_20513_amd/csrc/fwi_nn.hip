@@ -55,6 +55,7 @@ template <int NT, int MT>
 __global__ __launch_bounds__(256) void k_conv3x3(const bf16 *__restrict__ x,
                                                  const bf16 *__restrict__ w,
                                                  const float *__restrict__ bias,
+                                                 const bf16 *__restrict__ mask,
                                                  bf16 *__restrict__ y, int N, int H, int W,
                                                  int Ci, int Co, int relu) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -121,6 +122,7 @@ __global__ __launch_bounds__(256) void k_conv3x3(const bf16 *__restrict__ x,
                 if (po < P) {
                     float v = acc[m][j][r] + bb;
                     if (relu) v = fmaxf(v, 0.f);
+                    if (mask && !((float)mask[po * Co + co] > 0.f)) v = 0.f;
                     y[po * Co + co] = (bf16)v;
                 }
             }
@@ -147,6 +149,7 @@ template <int BN, int BM>
 __global__ __launch_bounds__(256) void k_conv3x3_lds(const bf16 *__restrict__ x,
                                                      const bf16 *__restrict__ w,
                                                      const float *__restrict__ bias,
+                                                     const bf16 *__restrict__ mask,
                                                      bf16 *__restrict__ y, int N, int H, int W,
                                                      int Ci, int Co, int relu) {
     static_assert(BM == 64 || BM == 128, "64 or 128 pixels per block");
@@ -261,6 +264,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_lds(const bf16 *__restrict__ x,
                 if (po < P) {
                     float v = acc[m][n][r] + bb;
                     if (relu) v = fmaxf(v, 0.f);
+                    if (mask && !((float)mask[po * Co + co] > 0.f)) v = 0.f;
                     y[po * Co + co] = (bf16)v;
                 }
             }
@@ -288,10 +292,11 @@ __global__ __launch_bounds__(256) void k_conv3x3_lds(const bf16 *__restrict__ x,
 // layers of 64 and 128 channels by the start of a block, about 11 us (32 images
 // of 64 x 64, 64 channels: 28.6 -> 20.7 us).  256 channels would need 288
 // registers of weights per lane: one wave per SIMD, slower (70 -> 91 us).
-template <int CI, int CT, int CG, int PG, bool KXC>
+template <int CI, int CT, int CG, int PG, bool KXC, bool MASK>
 __global__ __launch_bounds__(256) void k_conv3x3_rows(const bf16 *__restrict__ x,
                                                       const bf16 *__restrict__ w,
                                                       const float *__restrict__ bias,
+                                                      const bf16 *__restrict__ mask,
                                                       bf16 *__restrict__ y, int H, int W, int Co,
                                                       int relu, int strip, int nstrip, int rows,
                                                       int nrow) {
@@ -365,6 +370,16 @@ __global__ __launch_bounds__(256) void k_conv3x3_rows(const bf16 *__restrict__ x
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
             const int p0 = (pg * PT + pt0) * 16 + (lane & 15);
+            const size_t o0 = (((size_t)n * H + yo) * W + xs + p0) * Co + co0 + 4 * (lane >> 4);
+            bf16x4 mk[NP][CT];                               // in flight during the products
+            if (MASK)
+#pragma unroll
+                for (int i = 0; i < NP; ++i)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct)
+                        if (p0 + 16 * i < sw)
+                            mk[i][ct] = *reinterpret_cast<const bf16x4 *>(
+                                mask + o0 + (size_t)16 * i * Co + 16 * ct);
 #pragma unroll
             for (int ky = 0; ky < 3; ++ky) {
                 const bf16 *row = &ring[(k0 + ky) & 3][p0 * PITCH + kq];
@@ -392,9 +407,8 @@ __global__ __launch_bounds__(256) void k_conv3x3_rows(const bf16 *__restrict__ x
             }
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
-                const int p = p0 + 16 * i;
-                if (p >= sw) continue;
-                bf16 *out = y + (((size_t)n * H + yo) * W + xs + p) * Co + co0 + 4 * (lane >> 4);
+                if (p0 + 16 * i >= sw) continue;
+                bf16 *out = y + o0 + (size_t)16 * i * Co;
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     bf16x4 v;
@@ -402,6 +416,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_rows(const bf16 *__restrict__ x
                     for (int r = 0; r < 4; ++r) {
                         float f = acc[i][ct][r] + bb[ct][r];
                         if (relu) f = fmaxf(f, 0.f);
+                        if (MASK && !((float)mk[i][ct][r] > 0.f)) f = 0.f;
                         v[r] = (bf16)f;
                     }
                     *reinterpret_cast<bf16x4 *>(out + 16 * ct) = v;
@@ -449,20 +464,20 @@ double row_use(int W, int bw) {
 }
 
 template <int CI, int CT, int CG, int PG>
-hipError_t launch_rows(const bf16 *x, const bf16 *w, const float *bias, bf16 *y, int N, int H,
-                       int W, int Co, int relu, bool kxc, hipStream_t st) {
+hipError_t launch_rows(const bf16 *x, const bf16 *w, const float *bias, const bf16 *mask, bf16 *y,
+                       int N, int H, int W, int Co, int relu, bool kxc, hipStream_t st) {
     constexpr int BW = 4096 / CI;
     const int nstrip = (W + BW - 1) / BW, strip = (W + nstrip - 1) / nstrip;
     const int nco = Co / (16 * CT * CG);
     const int bands = row_bands((long long)N * nstrip * nco, H);
     const int rows = (H + bands - 1) / bands, nrow = (H + rows - 1) / rows;
     const dim3 grid((unsigned)(N * nrow * nstrip), (unsigned)nco);
-    if (kxc)
-        hipLaunchKernelGGL((k_conv3x3_rows<CI, CT, CG, PG, true>), grid, dim3(256), 0, st, x, w,
-                           bias, y, H, W, Co, relu, strip, nstrip, rows, nrow);
-    else
-        hipLaunchKernelGGL((k_conv3x3_rows<CI, CT, CG, PG, false>), grid, dim3(256), 0, st, x, w,
-                           bias, y, H, W, Co, relu, strip, nstrip, rows, nrow);
+    auto kernel = kxc ? (mask ? k_conv3x3_rows<CI, CT, CG, PG, true, true>
+                              : k_conv3x3_rows<CI, CT, CG, PG, true, false>)
+                      : (mask ? k_conv3x3_rows<CI, CT, CG, PG, false, true>
+                              : k_conv3x3_rows<CI, CT, CG, PG, false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, x, w, bias, mask, y, H, W, Co, relu, strip,
+                       nstrip, rows, nrow);
     return hipGetLastError();
 }
 
@@ -1014,7 +1029,7 @@ __global__ void k_pool(const bf16 *__restrict__ x, bf16 *__restrict__ y, int N, 
     y[i] = (bf16)(0.25f * s);
 }
 __global__ void k_pool_bwd(const bf16 *__restrict__ dy, const bf16 *__restrict__ s,
-                           bf16 *__restrict__ dx, int N, int H, int W, int C) {
+                           const bf16 *__restrict__ mask, bf16 *__restrict__ dx, int N, int H, int W, int C) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)N * H * W * C) return;
     const int c = (int)(i % C);
@@ -1023,6 +1038,7 @@ __global__ void k_pool_bwd(const bf16 *__restrict__ dy, const bf16 *__restrict__
     const size_t n = r / ((size_t)W * H);
     float v = 0.25f * (float)dy[((n * (H / 2) + yy / 2) * (W / 2) + xx / 2) * C + c];
     if (s) v += (float)s[i];
+    if (mask && !((float)mask[i] > 0.f)) v = 0.f;
     dx[i] = (bf16)v;
 }
 
@@ -1040,8 +1056,8 @@ __global__ void k_up_add(const bf16 *__restrict__ x, const bf16 *__restrict__ s,
     if (s) v += (float)s[i];
     y[i] = (bf16)v;
 }
-__global__ void k_up_bwd(const bf16 *__restrict__ dy, bf16 *__restrict__ dx, int N, int Hi,
-                         int Wi, int C) {
+__global__ void k_up_bwd(const bf16 *__restrict__ dy, const bf16 *__restrict__ mask,
+                         bf16 *__restrict__ dx, int N, int Hi, int Wi, int C) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (size_t)N * Hi * Wi * C) return;
     const int c = (int)(i % C);
@@ -1050,8 +1066,9 @@ __global__ void k_up_bwd(const bf16 *__restrict__ dy, bf16 *__restrict__ dx, int
     const size_t n = r / ((size_t)Wi * Hi);
     const int W2 = 2 * Wi;
     const bf16 *p = dy + ((n * 2 * Hi + 2 * yy) * W2 + 2 * xx) * C + c;
-    dx[i] = (bf16)((float)p[0] + (float)p[C] + (float)p[(size_t)W2 * C] +
-                   (float)p[(size_t)W2 * C + C]);
+    float v = (float)p[0] + (float)p[C] + (float)p[(size_t)W2 * C] + (float)p[(size_t)W2 * C + C];
+    if (mask && !((float)mask[i] > 0.f)) v = 0.f;
+    dx[i] = (bf16)v;
 }
 
 __global__ void k_add(const bf16 *a, const bf16 *b,
@@ -1106,7 +1123,7 @@ __global__ void k_pool8(const bf16 *__restrict__ x, bf16 *__restrict__ y, int N,
 }
 
 __global__ void k_pool_bwd8(const bf16 *__restrict__ dy, const bf16 *__restrict__ s,
-                            bf16 *__restrict__ dx, int N, int H, int W, int C) {
+                            const bf16 *__restrict__ mask, bf16 *__restrict__ dx, int N, int H, int W, int C) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int C8 = C / 8;
     if (i >= (size_t)N * H * W * C8) return;
@@ -1123,6 +1140,12 @@ __global__ void k_pool_bwd8(const bf16 *__restrict__ dy, const bf16 *__restrict_
     } else {
 #pragma unroll
         for (int k = 0; k < 8; ++k) o[k] = (bf16)(0.25f * (float)g[k]);
+    }
+    if (mask) {
+        const bf16x8 m = ld8(mask + r * C + c);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (!((float)m[k] > 0.f)) o[k] = (bf16)0.f;
     }
     st8(dx + r * C + c, o);
 }
@@ -1148,8 +1171,8 @@ __global__ void k_up_add8(const bf16 *__restrict__ x, const bf16 *__restrict__ s
     st8(y + r * C + c, o);
 }
 
-__global__ void k_up_bwd8(const bf16 *__restrict__ dy, bf16 *__restrict__ dx, int N, int Hi,
-                          int Wi, int C) {
+__global__ void k_up_bwd8(const bf16 *__restrict__ dy, const bf16 *__restrict__ mask,
+                          bf16 *__restrict__ dx, int N, int Hi, int Wi, int C) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int C8 = C / 8;
     if (i >= (size_t)N * Hi * Wi * C8) return;
@@ -1165,6 +1188,12 @@ __global__ void k_up_bwd8(const bf16 *__restrict__ dy, bf16 *__restrict__ dx, in
 #pragma unroll
     for (int k = 0; k < 8; ++k)
         o[k] = (bf16)((float)a[k] + (float)b[k] + (float)d[k] + (float)e[k]);
+    if (mask) {
+        const bf16x8 m = ld8(mask + r * C + c);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (!((float)m[k] > 0.f)) o[k] = (bf16)0.f;
+    }
     st8(dx + r * C + c, o);
 }
 
@@ -1327,12 +1356,9 @@ int status(hipError_t e) { return e == hipSuccess ? FWI_NN_OK : FWI_NN_EHIP; }
 
 bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-}  // namespace
-
-extern "C" {
-
-int fwi_nn_conv3x3(const void *x, const void *w, const float *bias, void *y, int32_t N,
-                   int32_t H, int32_t W, int32_t Ci, int32_t Co, int32_t relu, void *stream) {
+// the convolution, and with a mask zero where that is not positive
+int conv3x3(const void *x, const void *w, const float *bias, const void *mask, void *y, int32_t N,
+            int32_t H, int32_t W, int32_t Ci, int32_t Co, int32_t relu, void *stream) {
     if (!x || !w || !y || N < 1 || H < 1 || W < 1 || H > 32768 || W > 32768 || Ci < 32 ||
         Co < 32 || Ci % 32 || Co % 32 || !al16(x) || !al16(w))
         return FWI_NN_EINVAL;
@@ -1341,6 +1367,7 @@ int fwi_nn_conv3x3(const void *x, const void *w, const float *bias, void *y, int
     const int64_t P = (int64_t)N * H * W;
     const bf16 *xb = static_cast<const bf16 *>(x);
     const bf16 *wb = static_cast<const bf16 *>(w);
+    const bf16 *mb = static_cast<const bf16 *>(mask);
     bf16 *yb = static_cast<bf16 *>(y);
     // LDS-tiled kernel when it still gives the chip enough blocks, with the
     // narrower channel tile where only that one does, and 64-pixel blocks
@@ -1356,21 +1383,21 @@ int fwi_nn_conv3x3(const void *x, const void *w, const float *bias, void *y, int
     // 32 of 70 x 18, 64 channels: 12.9 -> 18.3) or there is too little to win
     // against its start (64 -> 32 channels, 32 images of 18 x 130: 12.8 -> 14.3)
     const bool kxc = lds_blocks < 256;
-    if ((Ci <= 64 || Ci == 128) && (reinterpret_cast<uintptr_t>(y) & 7) == 0 &&
+    if ((Ci <= 64 || Ci == 128) && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(mask)) & 7) == 0 &&
         (kxc || (row_use(W, 4096 / Ci) >= (Ci == 128 ? 0.92 : 0.8) &&
                  !(Ci == 64 && Co == 32 && P < 1 << 17)))) {
         hipError_t e;
         if (Ci == 32)
-            e = Co % 64 == 0 ? launch_rows<32, 2, 2, 2>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st)
-                             : launch_rows<32, 2, 1, 4>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+            e = Co % 64 == 0 ? launch_rows<32, 2, 2, 2>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st)
+                             : launch_rows<32, 2, 1, 4>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
         else if (Ci == 128)
-            e = Co % 64 == 0 ? launch_rows<128, 1, 4, 1>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st)
-                             : launch_rows<128, 1, 2, 2>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+            e = Co % 64 == 0 ? launch_rows<128, 1, 4, 1>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st)
+                             : launch_rows<128, 1, 2, 2>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
         else if (Co % 128 == 0)
-            e = launch_rows<64, 2, 4, 1>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+            e = launch_rows<64, 2, 4, 1>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
         else
-            e = Co % 64 == 0 ? launch_rows<64, 2, 2, 2>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st)
-                             : launch_rows<64, 2, 1, 4>(xb, wb, bias, yb, N, H, W, Co, relu, kxc, st);
+            e = Co % 64 == 0 ? launch_rows<64, 2, 2, 2>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st)
+                             : launch_rows<64, 2, 1, 4>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
         return status(e);
     }
     if (lds_blocks >= 256) {
@@ -1379,25 +1406,72 @@ int fwi_nn_conv3x3(const void *x, const void *w, const float *bias, void *y, int
         const int bm = lds_blocks < 512 ? 64 : 128;
         const dim3 grid((unsigned)((P + bm - 1) / bm), (unsigned)(Co / bn));
         if (bn == 64 && bm == 128)
-            hipLaunchKernelGGL((k_conv3x3_lds<64, 128>), grid, dim3(256), 0, st, xb, wb, bias, yb,
+            hipLaunchKernelGGL((k_conv3x3_lds<64, 128>), grid, dim3(256), 0, st, xb, wb, bias, mb, yb,
                                N, H, W, Ci, Co, relu);
         else if (bn == 64)
-            hipLaunchKernelGGL((k_conv3x3_lds<64, 64>), grid, dim3(256), 0, st, xb, wb, bias, yb,
+            hipLaunchKernelGGL((k_conv3x3_lds<64, 64>), grid, dim3(256), 0, st, xb, wb, bias, mb, yb,
                                N, H, W, Ci, Co, relu);
         else if (bm == 128)
-            hipLaunchKernelGGL((k_conv3x3_lds<32, 128>), grid, dim3(256), 0, st, xb, wb, bias, yb,
+            hipLaunchKernelGGL((k_conv3x3_lds<32, 128>), grid, dim3(256), 0, st, xb, wb, bias, mb, yb,
                                N, H, W, Ci, Co, relu);
         else
-            hipLaunchKernelGGL((k_conv3x3_lds<32, 64>), grid, dim3(256), 0, st, xb, wb, bias, yb,
+            hipLaunchKernelGGL((k_conv3x3_lds<32, 64>), grid, dim3(256), 0, st, xb, wb, bias, mb, yb,
                                N, H, W, Ci, Co, relu);
         return status(hipGetLastError());
     }
     // small layers: 64-pixel blocks of 32-channel tiles (four times the
     // blocks of the LDS tiling)
     const dim3 grid((unsigned)((P + 63) / 64), (unsigned)(Co / 32));
-    hipLaunchKernelGGL((k_conv3x3<2, 1>), grid, dim3(256), 0, st, xb, wb, bias, yb, N, H, W, Ci,
+    hipLaunchKernelGGL((k_conv3x3<2, 1>), grid, dim3(256), 0, st, xb, wb, bias, mb, yb, N, H, W, Ci,
                        Co, relu);
     return status(hipGetLastError());
+}
+
+int pool2_bwd(const void *dy, const void *skip, const void *mask, void *dx, int32_t N, int32_t H,
+              int32_t W, int32_t C, void *stream) {
+    if (!dy || !dx || N < 1 || H < 2 || W < 2 || H % 2 || W % 2 || C < 1) return FWI_NN_EINVAL;
+    const size_t n = (size_t)N * H * W * C;
+    const bf16 *sb = static_cast<const bf16 *>(skip), *mb = static_cast<const bf16 *>(mask);
+    if (C % 8 == 0 && al16(dy) && al16(dx) && (!skip || al16(skip)) && (!mask || al16(mask)))
+        hipLaunchKernelGGL(k_pool_bwd8, dim3(blocks_for(n / 8)), dim3(256), 0,
+                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy), sb, mb,
+                           static_cast<bf16 *>(dx), N, H, W, C);
+    else
+        hipLaunchKernelGGL(k_pool_bwd, dim3(blocks_for(n)), dim3(256), 0,
+                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy), sb, mb,
+                           static_cast<bf16 *>(dx), N, H, W, C);
+    return status(hipGetLastError());
+}
+
+int up2_bwd(const void *dy, const void *mask, void *dx, int32_t N, int32_t Hi, int32_t Wi,
+            int32_t C, void *stream) {
+    if (!dy || !dx || N < 1 || Hi < 1 || Wi < 1 || C < 1) return FWI_NN_EINVAL;
+    const size_t n = (size_t)N * Hi * Wi * C;
+    const bf16 *mb = static_cast<const bf16 *>(mask);
+    if (C % 8 == 0 && al16(dy) && al16(dx) && (!mask || al16(mask)))
+        hipLaunchKernelGGL(k_up_bwd8, dim3(blocks_for(n / 8)), dim3(256), 0,
+                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy), mb,
+                           static_cast<bf16 *>(dx), N, Hi, Wi, C);
+    else
+        hipLaunchKernelGGL(k_up_bwd, dim3(blocks_for(n)), dim3(256), 0,
+                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy), mb,
+                           static_cast<bf16 *>(dx), N, Hi, Wi, C);
+    return status(hipGetLastError());
+}
+
+}  // namespace
+
+extern "C" {
+
+int fwi_nn_conv3x3(const void *x, const void *w, const float *bias, void *y, int32_t N,
+                   int32_t H, int32_t W, int32_t Ci, int32_t Co, int32_t relu, void *stream) {
+    return conv3x3(x, w, bias, nullptr, y, N, H, W, Ci, Co, relu, stream);
+}
+
+int fwi_nn_conv3x3_masked(const void *x, const void *w, const void *mask, void *y, int32_t N,
+                          int32_t H, int32_t W, int32_t Ci, int32_t Co, void *stream) {
+    if (!mask) return FWI_NN_EINVAL;
+    return conv3x3(x, w, nullptr, mask, y, N, H, W, Ci, Co, 0, stream);
 }
 
 int fwi_nn_flip(const void *w, void *wf, int32_t Ci, int32_t Co, void *stream) {
@@ -1514,18 +1588,13 @@ int fwi_nn_pool2(const void *x, void *y, int32_t N, int32_t H, int32_t W, int32_
 
 int fwi_nn_pool2_bwd_add(const void *dy, const void *skip, void *dx, int32_t N, int32_t H,
                          int32_t W, int32_t C, void *stream) {
-    if (!dy || !dx || N < 1 || H < 2 || W < 2 || H % 2 || W % 2 || C < 1) return FWI_NN_EINVAL;
-    const size_t n = (size_t)N * H * W * C;
-    const bf16 *sb = static_cast<const bf16 *>(skip);
-    if (C % 8 == 0 && al16(dy) && al16(dx) && (!skip || al16(skip)))
-        hipLaunchKernelGGL(k_pool_bwd8, dim3(blocks_for(n / 8)), dim3(256), 0,
-                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy), sb,
-                           static_cast<bf16 *>(dx), N, H, W, C);
-    else
-        hipLaunchKernelGGL(k_pool_bwd, dim3(blocks_for(n)), dim3(256), 0,
-                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy), sb,
-                           static_cast<bf16 *>(dx), N, H, W, C);
-    return status(hipGetLastError());
+    return pool2_bwd(dy, skip, nullptr, dx, N, H, W, C, stream);
+}
+
+int fwi_nn_pool2_bwd_masked(const void *dy, const void *skip, const void *mask, void *dx,
+                            int32_t N, int32_t H, int32_t W, int32_t C, void *stream) {
+    if (!mask) return FWI_NN_EINVAL;
+    return pool2_bwd(dy, skip, mask, dx, N, H, W, C, stream);
 }
 
 int fwi_nn_pool2_bwd(const void *dy, void *dx, int32_t N, int32_t H, int32_t W, int32_t C,
@@ -1550,17 +1619,13 @@ int fwi_nn_up2_add(const void *x, const void *skip, void *y, int32_t N, int32_t 
 
 int fwi_nn_up2_bwd(const void *dy, void *dx, int32_t N, int32_t Hi, int32_t Wi, int32_t C,
                    void *stream) {
-    if (!dy || !dx || N < 1 || Hi < 1 || Wi < 1 || C < 1) return FWI_NN_EINVAL;
-    const size_t n = (size_t)N * Hi * Wi * C;
-    if (C % 8 == 0 && al16(dy) && al16(dx))
-        hipLaunchKernelGGL(k_up_bwd8, dim3(blocks_for(n / 8)), dim3(256), 0,
-                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy),
-                           static_cast<bf16 *>(dx), N, Hi, Wi, C);
-    else
-        hipLaunchKernelGGL(k_up_bwd, dim3(blocks_for(n)), dim3(256), 0,
-                           static_cast<hipStream_t>(stream), static_cast<const bf16 *>(dy),
-                           static_cast<bf16 *>(dx), N, Hi, Wi, C);
-    return status(hipGetLastError());
+    return up2_bwd(dy, nullptr, dx, N, Hi, Wi, C, stream);
+}
+
+int fwi_nn_up2_bwd_masked(const void *dy, const void *mask, void *dx, int32_t N, int32_t Hi,
+                          int32_t Wi, int32_t C, void *stream) {
+    if (!mask) return FWI_NN_EINVAL;
+    return up2_bwd(dy, mask, dx, N, Hi, Wi, C, stream);
 }
 
 int fwi_nn_add(const void *a, const void *b, void *y, size_t n, void *stream) {

@@ -33,10 +33,10 @@ FWI_NN_OK = 0
 FWI_NN_MSE_BLOCKS = 512
 CPAD = 32                      # channels of the packed network input
 
-EXPORTED = ("fwi_nn_conv3x3", "fwi_nn_flip", "fwi_nn_flip_layers", "fwi_nn_wgrad_workspace",
+EXPORTED = ("fwi_nn_conv3x3", "fwi_nn_conv3x3_masked", "fwi_nn_flip", "fwi_nn_flip_layers", "fwi_nn_wgrad_workspace",
             "fwi_nn_wgrad",
             "fwi_nn_relu_bwd", "fwi_nn_pool2", "fwi_nn_pool2_bwd", "fwi_nn_pool2_bwd_add",
-            "fwi_nn_up2_add",
+            "fwi_nn_pool2_bwd_masked", "fwi_nn_up2_add", "fwi_nn_up2_bwd_masked",
             "fwi_nn_up2_bwd", "fwi_nn_add", "fwi_nn_mse", "fwi_nn_adam", "fwi_nn_to_bf16",
             "fwi_nn_pack4", "fwi_nn_unpack2")
 
@@ -49,6 +49,7 @@ def lib() -> ctypes.CDLL:
     if not _ready:
         vp, sz, i32, f32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32, ctypes.c_float
         L.fwi_nn_conv3x3.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
+        L.fwi_nn_conv3x3_masked.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
         L.fwi_nn_flip.argtypes = [vp, vp, i32, i32, vp]
         L.fwi_nn_flip_layers.argtypes = [vp, vp, i32, vp, vp, vp, vp]
         L.fwi_nn_wgrad_workspace.argtypes = [i32, i32, i32]
@@ -58,8 +59,10 @@ def lib() -> ctypes.CDLL:
         L.fwi_nn_pool2.argtypes = [vp, vp, i32, i32, i32, i32, vp]
         L.fwi_nn_pool2_bwd.argtypes = [vp, vp, i32, i32, i32, i32, vp]
         L.fwi_nn_pool2_bwd_add.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp]
+        L.fwi_nn_pool2_bwd_masked.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, vp]
         L.fwi_nn_up2_add.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp]
         L.fwi_nn_up2_bwd.argtypes = [vp, vp, i32, i32, i32, i32, vp]
+        L.fwi_nn_up2_bwd_masked.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp]
         L.fwi_nn_add.argtypes = [vp, vp, vp, sz, vp]
         L.fwi_nn_mse.argtypes = [vp, vp, vp, vp, vp, sz, i32, i32, vp]
         L.fwi_nn_adam.argtypes = [vp, vp, vp, vp, vp, sz, f32, f32, f32, f32, i32, vp]
@@ -116,6 +119,16 @@ def conv3x3(x, w, bias, y, N, H, W, Ci, Co, relu, stream=None):
         _need(bias, F32, Co, "bias")
     _ok(lib().fwi_nn_conv3x3(_p(x), _p(w), _p(bias), _p(y), N, H, W, Ci, Co, int(relu),
                              _s(stream)), "fwi_nn_conv3x3")
+
+
+def conv3x3_masked(x, w, mask, y, N, H, W, Ci, Co, stream=None):
+    """y = conv3x3(x, w) where mask > 0, else 0."""
+    _need(x, BF, N * H * W * Ci, "x")
+    _need(w, BF, Co * 9 * Ci, "w")
+    _need(mask, BF, N * H * W * Co, "mask")
+    _need(y, BF, N * H * W * Co, "y")
+    _ok(lib().fwi_nn_conv3x3_masked(_p(x), _p(w), _p(mask), _p(y), N, H, W, Ci, Co, _s(stream)),
+        "fwi_nn_conv3x3_masked")
 
 
 def flip(w, wf, Ci, Co, stream=None):
@@ -179,6 +192,17 @@ def pool2_bwd_add(dy, skip, dx, N, H, W, C, stream=None):
         "fwi_nn_pool2_bwd_add")
 
 
+def pool2_bwd_masked(dy, skip, mask, dx, N, H, W, C, stream=None):
+    """dx = pool2_bwd(dy) + skip where mask > 0, else 0 (skip may be None)."""
+    _need(dy, BF, N * (H // 2) * (W // 2) * C, "dy")
+    if skip is not None:
+        _need(skip, BF, N * H * W * C, "skip")
+    _need(mask, BF, N * H * W * C, "mask")
+    _need(dx, BF, N * H * W * C, "dx")
+    _ok(lib().fwi_nn_pool2_bwd_masked(_p(dy), _p(skip), _p(mask), _p(dx), N, H, W, C, _s(stream)),
+        "fwi_nn_pool2_bwd_masked")
+
+
 def up2_add(x, skip, y, N, Ho, Wo, C, stream=None):
     _need(x, BF, N * (Ho // 2) * (Wo // 2) * C, "x")
     _need(y, BF, N * Ho * Wo * C, "y")
@@ -191,6 +215,15 @@ def up2_bwd(dy, dx, N, Hi, Wi, C, stream=None):
     _need(dy, BF, N * 4 * Hi * Wi * C, "dy")
     _need(dx, BF, N * Hi * Wi * C, "dx")
     _ok(lib().fwi_nn_up2_bwd(_p(dy), _p(dx), N, Hi, Wi, C, _s(stream)), "fwi_nn_up2_bwd")
+
+
+def up2_bwd_masked(dy, mask, dx, N, Hi, Wi, C, stream=None):
+    """dx = up2_bwd(dy) where mask > 0, else 0."""
+    _need(dy, BF, 4 * N * Hi * Wi * C, "dy")
+    _need(mask, BF, N * Hi * Wi * C, "mask")
+    _need(dx, BF, N * Hi * Wi * C, "dx")
+    _ok(lib().fwi_nn_up2_bwd_masked(_p(dy), _p(mask), _p(dx), N, Hi, Wi, C, _s(stream)),
+        "fwi_nn_up2_bwd_masked")
 
 
 def add(a, b, y, n, stream=None):
@@ -436,14 +469,15 @@ class Net:
         """dy: gradient of the loss w.r.t. the output [N][H][W][32] bf16.
         Fills self.grad (weights and biases of every layer).
 
-        Going backwards, G_k (the gradient w.r.t. the output of layer k)
-        becomes dz_k = relu'(out_k) * G_k, which gives the weight gradient
-        and, through the flipped weights, D_k = the gradient w.r.t. the
-        layer input.  D_k goes to the producer of that input: straight to
-        layer k-1; through the adjoint of pooling (plus the skip gradient
-        kept from the decoder) to the encoder output of the level above; or,
-        at a decoder merge up(r) + s, to the skip buffer of s and through
-        the adjoint of upsampling to r."""
+        Going backwards, dz_k = relu'(out_k) G_k, with G_k the gradient
+        w.r.t. the output of layer k, gives the weight gradient and, through
+        the flipped weights, D_k = the gradient w.r.t. the layer input.  D_k
+        goes to the producer of that input: straight to layer k-1; through
+        the adjoint of pooling (plus the skip gradient kept from the
+        decoder) to the encoder output of the level above; or, at a decoder
+        merge up(r) + s, to the skip buffer of s and through the adjoint of
+        upsampling to r.  The kernel that completes G_{k-1} multiplies it by
+        relu'(out_{k-1}) as it stores it: every layer but the last has one."""
         N, H, W = self._shape
         _need(dy, BF, N * H * W * CPAD, "dy")
         hw = [(H >> l, W >> l) for l in range(4)]
@@ -453,36 +487,32 @@ class Net:
             return next(b for b in bufs if all(b is not u for u in used))
 
         flip_layers(self.wbf, self._wflip, *self._flip_table)
-        cur = dy
+        dz = dy
         for k in range(len(LAYERS) - 1, -1, -1):
-            name, ci, co, lv, relu = LAYERS[k]
+            name, ci, co, lv, _ = LAYERS[k]
             h, w = hw[lv]
-            if relu:
-                dz = other(cur)
-                relu_bwd(self.out[k], cur, dz, N * h * w * co)
-            else:
-                dz = cur
             wgrad(self._input_of(k, self._x), dz, self.gw(k), self.gb(k), N, h, w, ci, co,
                   self.nsplit[k], self.wsg)
             if k == 0:
                 break
             wo = self.offs[k][0]
             wf = self._wflip[wo:wo + ci * 9 * co]
-            merge = name in ("d2a", "d1a", "d0a")
-            dx = self.gskip[lv] if merge else other(dz, cur)
-            conv3x3(dz, wf, None, dx, N, h, w, co, ci, False)
+            mask = self.out[k - 1]
             if name in ("e1a", "e2a", "e3a"):
                 hp, wp = hw[lv - 1]
-                g = other(dx)
-                pool2_bwd_add(dx, self.gskip[lv - 1], g, N, hp, wp, ci)
-                cur = g
-            elif merge:
+                dx = other(dz)
+                g = other(dz, dx)
+                conv3x3(dz, wf, None, dx, N, h, w, co, ci, False)
+                pool2_bwd_masked(dx, self.gskip[lv - 1], mask, g, N, hp, wp, ci)
+            elif name in ("d2a", "d1a", "d0a"):
                 hi, wi = hw[lv + 1]
                 g = other(dz)
-                up2_bwd(dx, g, N, hi, wi, ci)
-                cur = g
+                conv3x3(dz, wf, None, self.gskip[lv], N, h, w, co, ci, False)
+                up2_bwd_masked(self.gskip[lv], mask, g, N, hi, wi, ci)
             else:
-                cur = dx
+                g = other(dz)
+                conv3x3_masked(dz, wf, mask, g, N, h, w, co, ci)
+            dz = g
 
     def adam_step(self, lr, beta1=0.9, beta2=0.999, eps=1e-8):
         self.step += 1
