@@ -115,26 +115,7 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
         o.fn = std::move(fn);
         ops.push_back(std::move(o));
     };
-    // E and the full state (H, CPML memories) from (esrc, ssrc) to (edst,
-    // sdst), as copy_state and one E copy would do
-    auto copies = [&](Key k, float *edst, const float *esrc, const State &sdst,
-                      const State &ssrc) {
-        const unsigned long long S = (unsigned long long)d.S, f = S * d.plane;
-        Op o;
-        o.key = k;
-        o.kind = OP_COPY;
-        o.prob = ip;
-        o.cp = {{edst, esrc, f},
-                {sdst.Hx, ssrc.Hx, f},
-                {sdst.Hy, ssrc.Hy, f},
-                {sdst.phx, ssrc.phx, S * d.ys},
-                {sdst.phy, ssrc.phy, S * d.xs},
-                {sdst.pex, ssrc.pex, S * d.xs},
-                {sdst.pey, ssrc.pey, S * d.ys}};
-        ops.push_back(std::move(o));
-    };
     const size_t field = (size_t)d.S * d.plane;
-    const size_t fbytes = field * sizeof(float);
     const int D = L.pass;
     float *Ca = P.f(L.off_Ca), *Cs = P.f(L.off_Cs);
     const State fs[2] = {P.state(L.off_fwd[0], false), P.state(L.off_fwd[1], false)};
@@ -145,34 +126,28 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
     call({{0, 0, 0, 0}}, [=](hipStream_t st) {
         return launch_coefficients(u.eps_r, u.sigma, Ca, Cs, d.NX, d.NY, d.pitch, d.dt, st);
     });
-    call({{0, 0, 0, 1}}, [=](hipStream_t st) { return ok(zero_state(fs[0], d, false, st)); });
-    call({{0, 0, 0, 2}}, [=](hipStream_t st) { return launch_fill(P.slot(0), field, 0.f, st); });
+    const State first = P.checkpoint(0);
+    call({{0, 0, 0, 1}}, [=](hipStream_t st) { return ok(zero_state(first, d, true, st)); });
 
     // phase 1: forward sweep; E ping-pongs between slots 0 and 1, the full
-    // state is copied out at the start of every K-step segment
+    // state goes to a checkpoint, and on from there, every K steps
     FwdStreamArgs a = fwd_args(P);
     a.record = 1;
     int cur = 0, e = 0;
     for (int n0 = 0; n0 < d.nt; n0 += L.K) {
         const int n1 = std::min(d.nt, n0 + L.K);
         const int c = n0 / L.K;
-        float *cp = P.f(L.off_ckpt + (size_t)c * L.ckpt_stride);
-        const State cst = P.state(L.off_ckpt + (size_t)c * L.ckpt_stride + align_up(fbytes), false);
-        copies({{1, n0, 0, 0}}, cp, P.slot(e), cst, fs[cur]);
         for (int n = n0; n < n1; n += D) {
+            const bool to = n + D >= n1 && c + 1 < L.ncp;
+            const State in = n == n0 ? P.checkpoint(c) : fs[cur];
+            const State out = to ? P.checkpoint(c + 1) : fs[cur ^ 1];
             a.n = n;
             a.nlev = std::min(D, n1 - n);
-            a.E_in = P.slot(e);
+            a.E_in = n == n0 ? in.E : P.slot(e);
             e ^= 1;
-            a.E_out = P.slot(e);
+            a.E_out = to ? out.E : P.slot(e);
             a.E_lev = nullptr;
-            a.cur = cur;
-            a.Hx_in = fs[cur].Hx;
-            a.Hy_in = fs[cur].Hy;
-            a.Hx_out = fs[cur ^ 1].Hx;
-            a.Hy_out = fs[cur ^ 1].Hy;
-            a.psi_in = fs[cur].phx;
-            a.psi_out = fs[cur ^ 1].phx;
+            set_states(a, in, out);
             Op o;
             o.key = {{1, n, 1, 0}};
             o.kind = OP_FWD;
@@ -197,17 +172,22 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
     call({{3, 0, 0, 2}}, [=](hipStream_t st) { return launch_fill(S2, field, 0.f, st); });
 
     // phase 4: segments last first, keyed by their index so that the same
-    // time window of every problem lines up: restore the checkpoint, re-run
-    // the segment into slots 0..K, then the adjoint through them
+    // time window of every problem lines up: re-run the segment from its
+    // checkpoint into slots 1..K, then the adjoint through it (slot 0: the
+    // checkpoint's E)
     AdjStreamArgs b = adj_args(P);
     int acur = 0;
     constexpr int kSegBase = 1 << 28;
     for (int c = L.ncp - 1; c >= 0; --c) {
         const int n0 = c * L.K, n1 = std::min(d.nt, n0 + L.K);
         const int X = kSegBase - c;
-        const float *cp = P.f(L.off_ckpt + (size_t)c * L.ckpt_stride);
-        const State cst = P.state(L.off_ckpt + (size_t)c * L.ckpt_stride + align_up(fbytes), false);
-        copies({{4, X, 0, 0}}, P.slot(0), cp, fs[0], cst);
+        const State from = P.checkpoint(c);
+        Op cp;
+        cp.key = {{4, X, 0, 0}};
+        cp.kind = OP_COPY;
+        cp.prob = ip;
+        cp.cp = {{P.slot(0), from.E, (unsigned long long)field}};
+        ops.push_back(std::move(cp));
         int fcur = 0, j = 0;
         FwdStreamArgs f = fwd_args(P);
         f.record = 0;
@@ -217,13 +197,7 @@ void record(int ip, Problem &p, char *ws, std::vector<Op> &ops) {
             f.E_in = P.slot(n - n0);
             f.E_lev = P.slot(n + 1 - n0);
             f.E_out = nullptr;
-            f.cur = fcur;
-            f.Hx_in = fs[fcur].Hx;
-            f.Hy_in = fs[fcur].Hy;
-            f.Hx_out = fs[fcur ^ 1].Hx;
-            f.Hy_out = fs[fcur ^ 1].Hy;
-            f.psi_in = fs[fcur].phx;
-            f.psi_out = fs[fcur ^ 1].phx;
+            set_states(f, n == n0 ? from : fs[fcur], fs[fcur ^ 1]);
             Op o;
             o.key = {{4, X, 1, j}};
             o.kind = OP_FWD;

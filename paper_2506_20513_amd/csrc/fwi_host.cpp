@@ -456,18 +456,6 @@ int zero_state(const State &s, const Dims &d, bool with_e, hipStream_t st) {
     return FWI_OK;
 }
 
-int copy_state(const State &dst, const State &src, const Dims &d, hipStream_t st) {
-    const size_t S = d.S;
-    const size_t f = S * d.plane * sizeof(float);
-    FWI_TRY(hipMemcpyAsync(dst.Hx, src.Hx, f, hipMemcpyDeviceToDevice, st));
-    FWI_TRY(hipMemcpyAsync(dst.Hy, src.Hy, f, hipMemcpyDeviceToDevice, st));
-    FWI_TRY(hipMemcpyAsync(dst.phx, src.phx, S * d.ys * sizeof(float), hipMemcpyDeviceToDevice, st));
-    FWI_TRY(hipMemcpyAsync(dst.phy, src.phy, S * d.xs * sizeof(float), hipMemcpyDeviceToDevice, st));
-    FWI_TRY(hipMemcpyAsync(dst.pex, src.pex, S * d.xs * sizeof(float), hipMemcpyDeviceToDevice, st));
-    FWI_TRY(hipMemcpyAsync(dst.pey, src.pey, S * d.ys * sizeof(float), hipMemcpyDeviceToDevice, st));
-    return FWI_OK;
-}
-
 Tiling tiling(const Ptrs &P) {
     const Layout &L = *P.L;
     Tiling t;
@@ -492,8 +480,6 @@ StreamCold make_cold(const Ptrs &P, const fwi_geom *g, float *traces,
     const Layout &L = *P.L;
     StreamCold c;
     c.p = P.prof();
-    c.fs[0] = P.state(L.off_fwd[0], false);
-    c.fs[1] = P.state(L.off_fwd[1], false);
     if (L.mode != FWI_SAVE_NONE) {
         c.as[0] = P.state(L.off_adj[0], true);
         c.as[1] = P.state(L.off_adj[1], true);
@@ -518,7 +504,7 @@ FwdStreamArgs fwd_args(const Ptrs &P) {
     FwdStreamArgs a;
     a.NX = d.NX; a.NY = d.NY; a.npml = d.npml; a.pitch = d.pitch;
     a.W = d.W; a.S = d.S; a.R = d.R; a.nt = d.nt;
-    a.n = 0; a.nlev = 0; a.cur = 0; a.record = 0;
+    a.n = 0; a.nlev = 0; a.record = 0;
     a.tl = tiling(P);
     a.plane = d.plane; a.xs = d.xs; a.ys = d.ys;
     a.lev_stride = (size_t)d.S * d.plane;
@@ -536,6 +522,15 @@ FwdStreamArgs fwd_args(const Ptrs &P) {
     a.psi_x = align_up((size_t)d.S * d.xs * sizeof(float)) / sizeof(float);
     a.cold = reinterpret_cast<const StreamCold *>(P.base + L.off_cold);
     return a;
+}
+
+void set_states(FwdStreamArgs &a, const State &in, const State &out) {
+    a.Hx_in = in.Hx;
+    a.Hy_in = in.Hy;
+    a.psi_in = in.phx;
+    a.Hx_out = out.Hx;
+    a.Hy_out = out.Hy;
+    a.psi_out = out.phx;
 }
 
 AdjStreamArgs adj_args(const Ptrs &P) {
@@ -666,27 +661,28 @@ int setup(const Ptrs &P, const fwi_geom *g, const StreamCold &cold, const float 
 // Forward steps [n0, n1) in passes of up to L.pass steps.  E of the pass
 // starting at n is read from ein(n); per-level E goes to elev(n) (history /
 // segment) or, when elev returns null, the final E of the pass to eout(n).
-// The H / CPML state ping-pongs between fwd[cur] and fwd[cur ^ 1].
+// The H / CPML state ping-pongs between the two forward states from the first
+// on; the first pass reads it (and a state's E, if any, instead of ein) from
+// `from`, the last one writes it (E instead of eout) to `to`, unless null: a
+// checkpoint is written and read by the passes around it, without a copy.
 template <class EIn, class EOut, class ELev>
-int forward_passes(const Ptrs &P, FwdStreamArgs a, int n0, int n1, int &cur, EIn ein,
-                   EOut eout, ELev elev, bool record, hipStream_t st, Timer &tm) {
+int forward_passes(const Ptrs &P, FwdStreamArgs a, int n0, int n1, const State *from,
+                   const State *to, EIn ein, EOut eout, ELev elev, bool record, hipStream_t st,
+                   Timer &tm) {
     const Layout &L = *P.L;
-    State fs[2] = {P.state(L.off_fwd[0], false), P.state(L.off_fwd[1], false)};
+    const State fs[2] = {P.state(L.off_fwd[0], false), P.state(L.off_fwd[1], false)};
+    int cur = 0;
     a.record = record ? 1 : 0;
     const double all = (double)L.d.NX * L.d.NY * L.d.S;
     for (int n = n0; n < n1; n += L.pass) {
+        const State *in = n == n0 && from ? from : nullptr;
+        const State *out = n + L.pass >= n1 && to ? to : nullptr;
         a.n = n;
         a.nlev = std::min(L.pass, n1 - n);
-        a.E_in = ein(n);
+        a.E_in = in ? in->E : ein(n);
         a.E_lev = elev(n);
-        a.E_out = a.E_lev ? nullptr : eout(n);
-        a.cur = cur;
-        a.Hx_in = fs[cur].Hx;
-        a.Hy_in = fs[cur].Hy;
-        a.Hx_out = fs[cur ^ 1].Hx;
-        a.Hy_out = fs[cur ^ 1].Hy;
-        a.psi_in = fs[cur].phx;
-        a.psi_out = fs[cur ^ 1].phx;
+        a.E_out = a.E_lev ? nullptr : out ? out->E : eout(n);
+        set_states(a, in ? *in : fs[cur], out ? *out : fs[cur ^ 1]);
         FWI_TRY(tm.run(a.E_lev ? K_FWD_REFWD : K_FWD_SWEEP, all * a.nlev,
                        [&] { return launch_fwd_stream(a, st); }));
         cur ^= 1;
@@ -699,35 +695,29 @@ int forward_passes(const Ptrs &P, FwdStreamArgs a, int n0, int n1, int &cur, EIn
 int forward_run(const Layout &L, void *ws, bool record, hipStream_t st, Timer &tm) {
     const Dims &d = L.d;
     Ptrs P{static_cast<char *>(ws), &L};
-    State fs0 = P.state(L.off_fwd[0], false);
-    int rc = zero_state(fs0, d, false, st);
+    State first = L.ncp > 0 ? P.checkpoint(0) : P.state(L.off_fwd[0], false);
+    if (L.ncp == 0) first.E = P.slot(0);
+    int rc = zero_state(first, d, true, st);
     if (rc != FWI_OK) return rc;
-    FWI_TRY(launch_fill(P.slot(0), (size_t)d.S * d.plane, 0.f, st));
     FwdStreamArgs a = fwd_args(P);
-    int cur = 0;
     if (L.mode == FWI_SAVE_HISTORY) {
         return forward_passes(
-            P, a, 0, d.nt, cur, [&](int n) { return P.slot(n); },
-            [&](int) { return (float *)nullptr; }, [&](int n) { return P.slot(n + 1); },
-            record, st, tm);
+            P, a, 0, d.nt, nullptr, nullptr, [&](int n) { return P.slot(n); },
+            [&](int) { return (float *)nullptr; },
+            [&](int n) { return P.slot(n + 1); }, record, st, tm);
     }
     // E ping-pongs between slots 0 and 1 pass by pass; with checkpoints, the
-    // full state (E, H, CPML memories) is copied out every K steps
+    // full state (E, H, CPML memories) goes to one every K steps
     const int K = L.ncp > 0 ? L.K : d.nt;
     int e = 0;
     for (int n0 = 0; n0 < d.nt; n0 += K) {
-        const int n1 = std::min(d.nt, n0 + K);
-        if (L.ncp > 0) {
-            const int c = n0 / K;
-            char *cp = static_cast<char *>(ws) + L.off_ckpt + (size_t)c * L.ckpt_stride;
-            const size_t f = (size_t)d.S * d.plane * sizeof(float);
-            FWI_TRY(hipMemcpyAsync(cp, P.slot(e), f, hipMemcpyDeviceToDevice, st));
-            State cst = P.state(L.off_ckpt + (size_t)c * L.ckpt_stride + align_up(f), false);
-            rc = copy_state(cst, P.state(L.off_fwd[cur], false), d, st);
-            if (rc != FWI_OK) return rc;
-        }
+        const int c = n0 / K;
+        State from{}, to{};
+        if (L.ncp > 0) from = P.checkpoint(c);
+        if (c + 1 < L.ncp) to = P.checkpoint(c + 1);
         rc = forward_passes(
-            P, a, n0, n1, cur, [&](int) { return P.slot(e); },
+            P, a, n0, std::min(d.nt, n0 + K), L.ncp > 0 ? &from : nullptr,
+            c + 1 < L.ncp ? &to : nullptr, [&](int) { return P.slot(e); },
             [&](int) {
                 e ^= 1;
                 return P.slot(e);
@@ -793,19 +783,17 @@ int do_adjoint(const Layout &L, const float *eps_r, const float *sigma, float *g
         rc = adj_range(d.nt, 0);
         if (rc != FWI_OK) return rc;
     } else {
-        // segment by segment, last first: restore the checkpoint, re-run the
-        // segment forward into slots 0..K, then run the adjoint through it
+        // segment by segment, last first: re-run the segment forward from its
+        // checkpoint into slots 1..K, then run the adjoint through it (slot 0:
+        // the checkpoint's E)
         FwdStreamArgs fa = fwd_args(P);
-        const size_t f = field * sizeof(float);
         for (int c = L.ncp - 1; c >= 0; --c) {
             const int n0 = c * L.K, n1 = std::min(d.nt, n0 + L.K);
-            const size_t co = L.off_ckpt + (size_t)c * L.ckpt_stride;
-            FWI_TRY(hipMemcpyAsync(P.slot(0), P.base + co, f, hipMemcpyDeviceToDevice, st));
-            rc = copy_state(P.state(L.off_fwd[0], false), P.state(co + align_up(f), false), d, st);
-            if (rc != FWI_OK) return rc;
-            int cur = 0;
+            const State from = P.checkpoint(c);
+            FWI_TRY(hipMemcpyAsync(P.slot(0), from.E, field * sizeof(float),
+                                   hipMemcpyDeviceToDevice, st));
             rc = forward_passes(
-                P, fa, n0, n1, cur, [&](int n) { return P.slot(n - n0); },
+                P, fa, n0, n1, &from, nullptr, [&](int n) { return P.slot(n - n0); },
                 [&](int) { return (float *)nullptr; },
                 [&](int n) { return P.slot(n + 1 - n0); }, false, st, tm);
             if (rc != FWI_OK) return rc;

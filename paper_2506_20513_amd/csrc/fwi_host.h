@@ -87,6 +87,13 @@ struct Ptrs {
         st.pey = f(o);
         return st;
     }
+    // Checkpoint c: the state of step c K, E first.
+    State checkpoint(int c) const {
+        const size_t off = L->off_ckpt + (size_t)c * L->ckpt_stride;
+        State st = state(off + align_up((size_t)L->d.S * L->d.plane * sizeof(float)), false);
+        st.E = f(off);
+        return st;
+    }
     float *slot(int k) const {
         const Dims &d = L->d;
         return f(L->off_slots) + (size_t)k * d.S * d.plane;
@@ -103,12 +110,13 @@ struct Ptrs {
 // the copies, so the host arrays may be released on return).
 int upload_geometry(const Ptrs &P, const fwi_geom *g, const StreamCold &cold, hipStream_t st);
 int zero_state(const State &s, const Dims &d, bool with_e, hipStream_t st);
-int copy_state(const State &dst, const State &src, const Dims &d, hipStream_t st);
 Tiling tiling(const Ptrs &P);       // forward kernel
 Tiling tiling_adj(const Ptrs &P);   // adjoint kernel
 StreamCold make_cold(const Ptrs &P, const fwi_geom *g, float *traces, const float *residual,
                      float *src_adjoint);
 FwdStreamArgs fwd_args(const Ptrs &P);
+// the H / CPML states a forward pass reads and writes
+void set_states(FwdStreamArgs &a, const State &in, const State &out);
 AdjStreamArgs adj_args(const Ptrs &P);
 
 }  // namespace host

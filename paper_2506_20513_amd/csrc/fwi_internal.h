@@ -131,7 +131,6 @@ struct Tiling {
 // instead of holding them in scalar registers for the whole sweep.
 struct StreamCold {
     Profiles p;
-    State fs[2];              // forward H / CPML states (E unused)
     State as[2];              // adjoint states
     StreamGeom g;
     float *traces;            // [S][nt][R] or null
@@ -143,7 +142,6 @@ struct StreamCold {
 struct FwdStreamArgs {
     int NX, NY, npml, pitch, W, S, R, nt;
     int n, nlev;              // first step of the pass, steps in the pass (<= K)
-    int cur;                  // input state cold->fs[cur], output fs[cur ^ 1]
     int record;               // write traces
     Tiling tl;
     size_t plane, xs, ys, lev_stride;
@@ -155,7 +153,7 @@ struct FwdStreamArgs {
     const float *Hx_in, *Hy_in;
     float *Hx_out, *Hy_out;
     // the CPML memories of the same states (their phx), and the padded sizes
-    // of their y-strip and x-strip arrays (tile kernels)
+    // of their y-strip and x-strip arrays
     const float *psi_in;
     float *psi_out;
     size_t psi_y, psi_x;
@@ -175,7 +173,7 @@ struct AdjStreamArgs {
     const float *E_lev;       // forward Ez^{n_base + k} at E_lev + k * lev_stride
     const float *L_in, *LHx_in, *LHy_in;
     float *L_out, *LHx_out, *LHy_out;
-    const float *psi_in;      // as in FwdStreamArgs
+    const float *psi_in;      // as in FwdStreamArgs (tile kernels)
     float *psi_out;
     size_t psi_y, psi_x;
     float *S1, *S2;           // per-shot correlation sums [S][NY][pitch]

@@ -152,5 +152,24 @@ __device__ __forceinline__ int table_entry(const unsigned *boff, int nm, unsigne
     return lo;
 }
 
+// CPML memories of a state in their padded layout (see Ptrs::state): phx,
+// phy, pex, pey behind one another from `p` on.
+struct PsiPtr {
+    const float *p;
+    size_t y, x;         // padded sizes of a y-strip and an x-strip array
+    __device__ __forceinline__ float *phx(int s, size_t ys) const {
+        return const_cast<float *>(p) + (size_t)s * ys;
+    }
+    __device__ __forceinline__ float *phy(int s, size_t xs) const {
+        return const_cast<float *>(p) + y + (size_t)s * xs;
+    }
+    __device__ __forceinline__ float *pex(int s, size_t xs) const {
+        return const_cast<float *>(p) + y + x + (size_t)s * xs;
+    }
+    __device__ __forceinline__ float *pey(int s, size_t ys) const {
+        return const_cast<float *>(p) + y + 2 * x + (size_t)s * ys;
+    }
+};
+
 }  // namespace
 }  // namespace fwi

@@ -154,6 +154,7 @@ __device__ __forceinline__ void fwd_body(const FwdStreamArgs &a, const WaveTile 
     float hlast = 0.f;
     float nE = 0.f, nHx = 0.f, nHy = 0.f, nCa = 0.f, nCs = 0.f;
     float4 nPs = make_float4(0.f, 0.f, 0.f, 0.f);
+    const PsiPtr pin{a.psi_in, a.psi_y, a.psi_x}, pout{a.psi_out, a.psi_y, a.psi_x};
     auto load = [&](int r) {
         nE = nHx = nHy = nCa = nCs = 0.f;
         nPs = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -167,13 +168,13 @@ __device__ __forceinline__ void fwd_body(const FwdStreamArgs &a, const WaveTile 
             const int ry = yrow(r, NY, npml);
             if (ry >= 0) {
                 const unsigned q = (unsigned)(ry * P + i);
-                nPs.x = ldg(cold->fs[a.cur].phx + (size_t)s * a.ys, q);
-                nPs.w = ldg(cold->fs[a.cur].pey + (size_t)s * a.ys, q);
+                nPs.x = ldg(pin.phx(s, a.ys), q);
+                nPs.w = ldg(pin.pey(s, a.ys), q);
             }
             if (xp) {
                 const unsigned q = (unsigned)(r * a.W + cx);
-                nPs.y = ldg(cold->fs[a.cur].phy + (size_t)s * a.xs, q);
-                nPs.z = ldg(cold->fs[a.cur].pex + (size_t)s * a.xs, q);
+                nPs.y = ldg(pin.phy(s, a.xs), q);
+                nPs.z = ldg(pin.pex(s, a.xs), q);
             }
         }
     };
@@ -257,13 +258,13 @@ __device__ __forceinline__ void fwd_body(const FwdStreamArgs &a, const WaveTile 
                     stg(a.Hy_out + so, k, hy);
                     if (yp) {
                         const unsigned q2 = (unsigned)(ry * P + i);
-                        stg(cold->fs[a.cur ^ 1].phx + (size_t)s * a.ys, q2, ps.x);
-                        stg(cold->fs[a.cur ^ 1].pey + (size_t)s * a.ys, q2, ps.w);
+                        stg(pout.phx(s, a.ys), q2, ps.x);
+                        stg(pout.pey(s, a.ys), q2, ps.w);
                     }
                     if (xp) {
                         const unsigned q2 = (unsigned)(j * a.W + cx);
-                        stg(cold->fs[a.cur ^ 1].phy + (size_t)s * a.xs, q2, ps.y);
-                        stg(cold->fs[a.cur ^ 1].pex + (size_t)s * a.xs, q2, ps.z);
+                        stg(pout.phy(s, a.xs), q2, ps.y);
+                        stg(pout.pex(s, a.xs), q2, ps.z);
                     }
                 }
             }

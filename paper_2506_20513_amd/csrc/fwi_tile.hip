@@ -145,25 +145,6 @@ __device__ __forceinline__ unsigned rows_pml(ColdRef cold, int j0, int NY, int n
     return m;
 }
 
-// CPML memories of a state in their padded layout (see Ptrs::state): phx,
-// phy, pex, pey behind one another from `p` on.
-struct PsiPtr {
-    const float *p;
-    size_t y, x;         // padded sizes of a y-strip and an x-strip array
-    __device__ __forceinline__ float *phx(int s, size_t ys) const {
-        return const_cast<float *>(p) + (size_t)s * ys;
-    }
-    __device__ __forceinline__ float *phy(int s, size_t xs) const {
-        return const_cast<float *>(p) + y + (size_t)s * xs;
-    }
-    __device__ __forceinline__ float *pex(int s, size_t xs) const {
-        return const_cast<float *>(p) + y + x + (size_t)s * xs;
-    }
-    __device__ __forceinline__ float *pey(int s, size_t ys) const {
-        return const_cast<float *>(p) + y + 2 * x + (size_t)s * ys;
-    }
-};
-
 // ---------------------------------------------------------------------------
 // Forward: nlev <= D levels of k_fwd's step (fwi_stream.hip).
 template <int R>
