@@ -24,6 +24,12 @@ template <class T>
 __device__ __forceinline__ void stg(T *base, unsigned idx, T v) {
     *(FWI_AS_GLOBAL T *)((FWI_AS_GLOBAL char *)base + (size_t)(idx * (unsigned)sizeof(T))) = v;
 }
+// a store that is not read again before the caches have turned over
+template <class T>
+__device__ __forceinline__ void stg_nt(T *base, unsigned idx, T v) {
+    __builtin_nontemporal_store(v, (FWI_AS_GLOBAL T *)((FWI_AS_GLOBAL char *)base +
+                                                       (size_t)(idx * (unsigned)sizeof(T))));
+}
 template <class T>
 __device__ __forceinline__ T ldc(const T *base, unsigned idx) {
     return ((const FWI_AS_CONST T *)base)[idx];
