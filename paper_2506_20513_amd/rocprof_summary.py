@@ -59,13 +59,16 @@ def kernel_source_hash() -> str:
 
 def short_name(name: str) -> str | None:
     """The benchmark's name for a kernel of a trace: the single-problem
-    forward kernel k_fwd<K, TAIL, LEV> is k_fwd_sweep for LEV = 0 (only the
-    final state written) and k_fwd_reforward for LEV = 1 (every level's Ez
-    written); other kernels keep their own name."""
+    forward kernels k_fwd<K, TAIL, LEV> and k_fwd_tile<D, R, NW, LEV> are
+    k_fwd_sweep for LEV = 0 (only the final state written) and
+    k_fwd_reforward for LEV = 1 (every level's Ez written), k_adj_tile is
+    k_adj; other kernels keep their own name."""
     m = re.search(r"::(k_\w+)<([^>]*)>", name)
     if not m:
         return None
-    if m.group(1) == "k_fwd":
+    if m.group(1) == "k_adj_tile":
+        return "k_adj"
+    if m.group(1) in ("k_fwd", "k_fwd_tile"):
         lev = m.group(2).split(",")[-1].strip()
         return {"0": "k_fwd_sweep", "1": "k_fwd_reforward"}.get(lev, "k_fwd")
     return m.group(1)
