@@ -315,7 +315,7 @@ typedef struct fwi_batch_info {
     int32_t tune_rows[FWI_BATCH_MAX_TUNE];  /* and band height (0: default)   */
     double tune_ms[FWI_BATCH_MAX_TUNE];     /* its cost per time step, ms:
                                   (forward sweep + segment re-forward +
-                                  adjoint pass) / depth, each the largest
+                                  adjoint pass) / their steps, each the largest
                                   merged full-depth launch of its kind,
                                   best of 3                                 */
 } fwi_batch_info;

@@ -81,9 +81,12 @@ hipError_t ok(int rc) { return rc == FWI_OK ? hipSuccess : hipErrorUnknown; }
 
 // Temporal depth of the passes and row bands of height `rows`.  0: tiles of
 // one height for all problems (their passes share launches), the imaging sums
-// grouped by `depth`, or for a batch too large for them the streaming default
-// of each problem.  The checkpoint interval is a multiple of both depths, so
-// the workspace layout does not change.
+// grouped by `depth`, or at depth 8 for a batch too large for them the streaming
+// default of each problem.  At depth 4 tiles are faster for any batch: 12, 24 and
+// 48 models of 200 x 100 to 640 x 320, 8 shots: 504, 848, 1556 ms with streams,
+// 268, 562, 1121 with tiles (the merged launches read their arguments from a
+// table, which costs the streaming kernels registers).  The checkpoint interval
+// is a multiple of both depths, so the workspace layout does not change.
 void set_tiling(std::vector<Problem> &probs, int depth, int rows) {
     long long tiles = 0, cells = 0;
     for (const Problem &p : probs) {
@@ -94,7 +97,7 @@ void set_tiling(std::vector<Problem> &probs, int depth, int rows) {
         p.L.depth = depth;
         if (rows > 0)
             fixed_bands(p.L, rows, depth);
-        else if (use_tiles(cells))
+        else if (depth == kDepthSmall || use_tiles(depth, cells, tiles))
             set_tiles(p.L, pick_tile(tiles));
         else
             set_streams(p.L);
@@ -553,8 +556,8 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
         // time, for every candidate, the largest merged full-depth launch of
         // each pass kind (best of 3 each): the forward sweep, the segment
         // re-forward and the adjoint.  A gradient runs one of each per
-        // `depth` steps, so the cost per step is (sweep + re-forward +
-        // adjoint) / depth.  The largest launches are those where every
+        // pass (`depth` steps, or a tile pass's levels), so the cost per step is
+        // (sweep + re-forward + adjoint) / those.  The largest launches are those where every
         // problem takes part; the first adjoint launches hold only the
         // longest problems.  The re-forward and adjoint passes run on
         // whatever state the workspace holds (all of it allocated); their
@@ -580,9 +583,28 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
             return FWI_OK;
         };
         int tuned = 0;
+        double tile_cost = -1.0;
+        auto consider = [&](int dep, int h, double cost) {
+            if (tuned < FWI_BATCH_MAX_TUNE) {
+                plan->info.tune_depth[tuned] = dep;
+                plan->info.tune_rows[tuned] = h;
+                plan->info.tune_ms[tuned] = cost;
+                ++tuned;
+            }
+            if (cost < best * 0.98) {
+                best = cost;
+                depth = dep;
+                rows = h;
+            }
+        };
         for (int dep : depths) {
             for (int h : heights) {
                 set_tiling(probs, dep, h);
+                if (probs.front().L.tile && tile_cost >= 0.0) {
+                    // the same passes, only the imaging sums group otherwise
+                    consider(dep, h, tile_cost);
+                    continue;
+                }
                 rc = upload_all();
                 if (rc != FWI_OK) break;
                 build_schedule(probs, w, 0, S);
@@ -625,18 +647,9 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
                 else tr = tf;
                 if (rc == FWI_OK) rc = time_step(S.steps[fadj], ta);
                 if (rc != FWI_OK) break;
-                const double cost = ((double)tf + tr + ta) / dep;
-                if (tuned < FWI_BATCH_MAX_TUNE) {
-                    plan->info.tune_depth[tuned] = dep;
-                    plan->info.tune_rows[tuned] = h;
-                    plan->info.tune_ms[tuned] = cost;
-                    ++tuned;
-                }
-                if (cost < best * 0.98) {
-                    best = cost;
-                    depth = dep;
-                    rows = h;
-                }
+                const double cost = ((double)tf + tr + ta) / probs.front().L.pass;
+                if (probs.front().L.tile) tile_cost = cost;
+                consider(dep, h, cost);
             }
             if (rc != FWI_OK) break;
         }

@@ -143,16 +143,24 @@ double adj_waves(int depth) { return depth == kDepthLarge ? 3.0 : 4.0; }
 
 // Tiles or streams.  The streaming kernels read a field row once per pass and
 // pay a load latency per row; the tile kernels read a tile with its halo (1.8
-// times its cells) at once.  Up to kTileCells cells (all shots of the call)
-// the fields of a pass fit the 256 MB last-level cache or the chip is not full
-// of waves, and tiles are faster: one gradient took (streams -> tiles)
-// 148 x 148 x 1 shot, 800 steps: 19.4 -> 4.5 ms; 552 x 296 x 24 shots, 3000
-// steps: 146 -> 123 ms; 1040 x 640 x 24 shots (16 M cells), 96 steps:
-// 16.6 -> 15.3 ms; 2088 x 1064 x 4 shots (9 M), 96 steps: 9.6 -> 8.6 ms, but
-// with 16 shots (36 M) 27.7 -> 31.4 ms.
-constexpr long long kTileCells = 20LL << 20;
-
-bool use_tiles(long long cells) { return cells <= kTileCells; }
+// times its cells) at once and keep up to 48 x 48 cells of it.  On a chip not full
+// of waves tiles are faster, up to 15 M cells (all shots of the call) against
+// depth 8 and 7 M against depth 4: one gradient took (streams, tiles; ms)
+//   2088 x 1064, 96 steps   4 shots (9 M) 8.5, 7.9    6 (13 M) 12.1, 11.7
+//                           8 (18 M) 14.8, 15.5      16 (36 M) 23.0, 28.9
+//   552 x 296, 192 steps   24 shots (4 M) 9.7, 8.4   40 (6.5 M) 14.0, 13.8
+//   552 x 296, 96 steps    48 (8 M) 8.5, 9.1         96 (16 M) 15.6, 17.7
+// Beyond, 96 steps take 1.9 to 2.0 us per tile and at depth 4 0.9 to 1.0 ns per
+// cell, so against depth 4 it depends on how the grid fits its tiles: from 2050
+// cells per tile on (in brackets)
+//   1040 x 640, 96 steps (2161)    40 shots (27 M) 23.7, 23.3   56 33.6, 32.3
+//   480 x 480, 192 steps (2304)    48 (11 M) 20.3, 18.7
+//   740 x 540, 96 steps (2081)     24 (10 M) 9.6, 9.3     48 18.0, 18.2
+//   640 x 340, 192 steps (1943)    48 (10 M) 19.6, 21.1
+bool use_tiles(int depth, long long cells, long long tiles) {
+    if (depth == kDepthLarge) return cells <= 15LL << 20;
+    return cells <= 7LL << 20 || cells >= 2050 * tiles;
+}
 
 long long tile_count(const Dims &d) {
     constexpr int OX = 64 - 2 * kTileLevels, OY = kTileRowsLarge - 2 * kTileLevels;
@@ -189,8 +197,9 @@ void set_streams(Layout &L, int groups) {
 // The layout's decomposition, one of `groups` launches of its kind that share
 // the chip.
 void make_tiling(const Dims &d, Layout &L, int groups) {
-    if (use_tiles((long long)groups * d.S * d.NX * d.NY))
-        set_tiles(L, pick_tile(groups * tile_count(d)));
+    const long long cells = (long long)groups * d.S * d.NX * d.NY, tiles = groups * tile_count(d);
+    if (use_tiles(L.depth, cells, tiles))
+        set_tiles(L, pick_tile(tiles));
     else
         set_streams(L, groups);
 }

@@ -24,7 +24,7 @@ void make_tiling(const Dims &d, Layout &L, int groups = 1);
 // Whether that many cells (all shots) run on tiles; a problem's tiles of the
 // large height; the height for that many tiles in flight; tiles of height
 // `rows` for both kernels; the streaming decomposition.
-bool use_tiles(long long cells);
+bool use_tiles(int depth, long long cells, long long tiles);
 long long tile_count(const Dims &d);
 int pick_tile(long long tiles);
 void set_tiles(Layout &L, int rows);
