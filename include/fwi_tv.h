@@ -20,7 +20,8 @@
  * mu, lam > 0; the term added is the gradient of the Moreau envelope of TV.
  *
  * Memory: X and grad are device arrays [nfield][ny][nx] owned by the
- * caller; grad is read and updated in place.  ws is device scratch of at
+ * caller; grad is read and updated in place, and may be X itself (weight -1
+ * leaves the denoised model there).  ws is device scratch of at
  * least fwi_tv_workspace_bytes(nfield, ny, nx) bytes, 256-byte aligned.
  * mu, lam, weight are host arrays of nfield values (per-field settings).
  * The call is asynchronous on `stream` (hipStream_t, NULL = null stream).

@@ -138,6 +138,10 @@ __device__ __forceinline__ void bregman(float wx, float wy, float t, float &px, 
     py = zy - by;
 }
 
+__device__ __forceinline__ float add_term(float g, float x, float s, float u, float weight) {
+    return g + weight * (x - s * u);
+}
+
 // nit <= D iterations.  `first`: from U_0 = X / s and B = 0, with s from the
 // partial maxima (stored for the later launches); `last`: the term goes to grad
 // in place of U and B.
@@ -222,7 +226,7 @@ __global__ __launch_bounds__(64 * NW) void k_tv_tile(
         if (tr < D || tr >= D + OY || j >= ny || !own) continue;
         const size_t c = off + (size_t)j * nx + x0 + lane;
         if (last) {
-            grad[c] += p.weight[f] * (X[c] - s * u[r]);
+            grad[c] = add_term(grad[c], X[c], s, u[r], p.weight[f]);
         } else {
             Uo[c] = u[r];
             Bxo[c] = bx[r];
@@ -231,20 +235,40 @@ __global__ __launch_bounds__(64 * NW) void k_tv_tile(
     }
 }
 
+// The term for a grad that shares memory with X: the last tile launch reads X
+// over its tiles' halos, which neighbouring tiles must not have overwritten, so it
+// stores U instead and this one reads and writes each cell once (no __restrict__).
+__global__ __launch_bounds__(256) void k_tv_term(const float *X, const float *scale,
+                                                 const float *U, float *grad, size_t n,
+                                                 TvParams p) {
+    const int f = blockIdx.y;
+    const float s = scale[f];
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (s == 0.f || i >= n) return;      // all-zero field: its term is zero
+    const size_t c = f * n + i;
+    grad[c] = add_term(grad[c], X[c], s, U[c], p.weight[f]);
+}
+
 template <int D, int R, int NW>
 void run_tiles(const float *X, float *grad, int nfield, int ny, int nx, const TvParams &p,
                int iters, const Layout &L, char *w, int nb, hipStream_t st) {
     constexpr int OX = 64 - 2 * D, OY = NW * R - 2 * D;
     auto F = [&](size_t o) { return reinterpret_cast<float *>(w + o); };
     const dim3 grid((nx + OX - 1) / OX, (ny + OY - 1) / OY, nfield);
+    const size_t n = (size_t)ny * nx;
+    const uintptr_t a = reinterpret_cast<uintptr_t>(X), b = reinterpret_cast<uintptr_t>(grad);
+    const bool shared = (a < b ? b - a : a - b) < nfield * n * sizeof(float);
     int k = 0;
     for (int t = 0; t < iters; t += D, k ^= 1) {
         const int nit = std::min(D, iters - t);
         hipLaunchKernelGGL((k_tv_tile<D, R, NW>), grid, dim3(64 * NW), 0, st, X, F(L.part), nb,
                            F(L.scale), F(L.u[k]), F(L.bx[k]), F(L.by[k]), F(L.u[k ^ 1]),
                            F(L.bx[k ^ 1]), F(L.by[k ^ 1]), grad, ny, nx, p, nit, t == 0,
-                           t + nit == iters);
+                           t + nit == iters && !shared);
     }
+    if (shared)
+        hipLaunchKernelGGL(k_tv_term, dim3((unsigned)((n + 255) / 256), nfield), dim3(256), 0, st,
+                           X, F(L.scale), F(L.u[k]), grad, n, p);
 }
 
 }  // namespace
