@@ -27,6 +27,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "fwi_tv.h"
 
@@ -36,8 +37,9 @@ constexpr int kMaxBlocks = 1024;   // partial maxima per field
 constexpr size_t kAlign = 256;
 
 struct TvParams {
-    float mu[FWI_TV_MAX_FIELDS];
+    float mu[FWI_TV_MAX_FIELDS];      // both times a power of two (see fwi_tv_gradient)
     float lam[FWI_TV_MAX_FIELDS];
+    float t[FWI_TV_MAX_FIELDS];       // 1 / lam of the caller
     float weight[FWI_TV_MAX_FIELDS];
 };
 
@@ -121,7 +123,8 @@ __device__ __forceinline__ float div_by(float n, float d, float rd) {
 // square root and are corrected by their residuals, to within half a unit in
 // the last place and a little (the library's sqrt and division together take
 // three times the operations).  The smallest normal number in place of a
-// smaller square keeps the reciprocal finite: such a w is below every t.
+// smaller square keeps the reciprocal finite: such a w, below 1.1e-19 of the
+// field's largest value, is below every t of a lam up to 9e18.
 __device__ __forceinline__ void bregman(float wx, float wy, float t, float &px, float &py,
                                         float &bx, float &by) {
     const float m2 = fmaxf(fmaf(wx, wx, wy * wy), 1.17549435e-38f);
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(64 * NW) void k_tv_tile(
         s = scale[f];
     }
     if (s == 0.f) return;                // all-zero field: its term is zero
-    const float inv = 1.f / s, mu = p.mu[f], lam = p.lam[f], t = 1.f / lam;
+    const float inv = 1.f / s, mu = p.mu[f], lam = p.lam[f], t = p.t[f];
     const float den = mu + 8.f * lam, rden = 1.f / den;
     const size_t off = (size_t)f * ny * nx;
     const int x0 = (int)blockIdx.x * OX - D, y0 = (int)blockIdx.y * OY - D;
@@ -291,8 +294,13 @@ int fwi_tv_gradient(const float *X, float *grad, int32_t nfield, int32_t ny, int
     TvParams p{};
     for (int f = 0; f < nfield; ++f) {
         if (!(mu[f] > 0.f) || !(lam[f] > 0.f)) return -1;
-        p.mu[f] = mu[f];
-        p.lam[f] = lam[f];
+        // The U update is a ratio, homogeneous in mu and lam.  Where mu + 8 lam or
+        // its reciprocal could leave the normal numbers, both are scaled into them.
+        const float m = std::max(mu[f], lam[f]);
+        const int e = !std::isfinite(m) ? 0 : m > 0x1p100f ? -100 : m < 0x1p-100f ? 100 : 0;
+        p.mu[f] = std::ldexp(mu[f], e);
+        p.lam[f] = std::ldexp(lam[f], e);
+        p.t[f] = 1.f / lam[f];
         p.weight[f] = weight[f];
     }
     const Layout L = layout(nfield, ny, nx);
