@@ -318,7 +318,16 @@ int fwi_tv_gradient(const float *X, float *grad, int32_t nfield, int32_t ny, int
     // 100; and for the last kind against 4
     // iterations on 64 rows 2 x 1064 x 2088: 535 against 651.
     const size_t cells = (size_t)nfield * n;
-    if (cells <= (size_t)1 << 17)
+    // Of many cells, one iteration alone takes a halo of one cell (2 x 1064 x
+    // 2088: 28.5 -> 23.6 us; a thread per cell 26.3), and fields of a few rows the
+    // lowest tile, which wastes the fewest (20 iterations on 2 x 100000: 183 -> 57,
+    // a thread per cell 96; on two of 3 x 400000 that is still 546 against 382).
+    const bool many = cells > (size_t)1 << 17;
+    if (many && ny <= 6)
+        run_tiles<5, 3, 4>(X, grad, nfield, ny, nx, p, iters, L, w, nb, st);
+    else if (many && iters == 1)
+        run_tiles<1, 5, 8>(X, grad, nfield, ny, nx, p, iters, L, w, nb, st);
+    else if (!many)
         run_tiles<10, 4, 8>(X, grad, nfield, ny, nx, p, iters, L, w, nb, st);
     else if (cells <= (size_t)1 << 19)
         run_tiles<10, 3, 16>(X, grad, nfield, ny, nx, p, iters, L, w, nb, st);
