@@ -34,8 +34,10 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
 // m = floor((2^32 - 1) / d) + 1 = 2^32 / d + e, 0 < e <= 1.  Then n m / 2^32 =
 // n / d + n e / 2^32 with n e / 2^32 <= n / 2^32 < 1 / d, less than the
 // distance from n / d up to the next integer, so the floor is exact.  d = 1
-// (where m would overflow) is passed through.  The convolution kernels use
-// it with d = H or W <= 2^15 (checked by the host) and n < 2 d + 2^8.
+// (where m would overflow) is passed through.  Its users: the convolution and
+// weight-gradient kernels with d = H or W <= 2^15 (checked by the host) and n < 2 d
+// + 2^8; k_wgrad_rows with d <= 2^8 + 2 and n < 2^10; store_first_pieces with d
+// <= 2^8 pieces of a pixel and n < 64 d.
 struct SmallDiv {
     unsigned d, m;
     __device__ explicit SmallDiv(unsigned dd) : d(dd), m(dd > 1 ? 0xffffffffu / dd + 1u : 0u) {}
@@ -1382,13 +1384,14 @@ __global__ void k_to_bf16(const float *__restrict__ a, bf16 *__restrict__ b, siz
 // Network input / output conversion between float32 planes and NHWC bf16.
 __global__ void k_pack4(const float *__restrict__ planes, const float *__restrict__ scale,
                         bf16 *__restrict__ x, int N, int H, int W, int C) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)N * H * W * C) return;
-    const int c = (int)(i % C);
-    const size_t p = i / C;               // pixel index n*H*W + y*W + x
-    const size_t hw = (size_t)H * W;
-    const size_t n = p / hw, q = p % hw;
-    x[i] = c < 4 ? (bf16)(planes[(n * 4 + c) * hw + q] * scale[n * 4 + c]) : (bf16)0.f;
+    const size_t hw = (size_t)H * W, all = N * hw * C;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < all;
+         i += (size_t)gridDim.x * blockDim.x) {
+        const int c = (int)(i % C);
+        const size_t p = i / C;               // pixel index n*H*W + y*W + x
+        const size_t n = p / hw, q = p % hw;
+        x[i] = c < 4 ? (bf16)(planes[(n * 4 + c) * hw + q] * scale[n * 4 + c]) : (bf16)0.f;
+    }
 }
 // The same packing per pixel for C a multiple of 8 and x 16-byte aligned:
 // four scaled plane values and zero padding.  Bound by the zeros it writes
@@ -1777,12 +1780,15 @@ int fwi_nn_pack4(const float *planes, const float *scale, void *x, int32_t N, in
                  int32_t W, int32_t C, void *stream) {
     if (!planes || !scale || !x || N < 1 || H < 1 || W < 1 || C < 4) return FWI_NN_EINVAL;
     const size_t n = (size_t)N * H * W * C;
-    if (C % 8 == 0 && al16(x))
+    // past 2048 channels a thread per value: a wave would store its pixels' pieces
+    // one after another (2 x 2 pixels of 65536 channels: 554 and 7.5 us), and its
+    // piece indices outgrow the short division
+    if (C % 8 == 0 && C <= 2048 && al16(x))
         hipLaunchKernelGGL(k_pack4_px, dim3(blocks_for((size_t)N * H * W)), dim3(256), 0,
                            static_cast<hipStream_t>(stream), planes, scale,
                            static_cast<bf16 *>(x), N, H, W, C);
     else
-        hipLaunchKernelGGL(k_pack4, dim3(blocks_for(n)), dim3(256), 0,
+        hipLaunchKernelGGL(k_pack4, dim3(std::min(blocks_for(n), 1u << 22)), dim3(256), 0,
                            static_cast<hipStream_t>(stream), planes, scale,
                            static_cast<bf16 *>(x), N, H, W, C);
     return status(hipGetLastError());
