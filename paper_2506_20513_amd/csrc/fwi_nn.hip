@@ -1296,11 +1296,55 @@ __device__ __forceinline__ void store_first_pieces(bf16 *x, int nv, size_t w0, s
 // The same loss per pixel, for C a multiple of 8 and 16-byte aligned rows:
 // a thread reads the cout channels of a pixel it needs and writes the whole
 // dy row as 16-byte pieces (zero past cout), with no per-element division.
-__global__ __launch_bounds__(1024) void k_mse_px(const bf16 *__restrict__ y,
-                                                 const float *__restrict__ tgt,
-                                                 bf16 *__restrict__ dy,
-                                                 double *__restrict__ partial, size_t P, int C,
-                                                 int cout) {
+__global__ __launch_bounds__(256) void k_mse_px(const bf16 *__restrict__ y,
+                                                const float *__restrict__ tgt,
+                                                bf16 *__restrict__ dy,
+                                                double *__restrict__ partial, size_t P, int C,
+                                                int cout) {
+    __shared__ double red[256];
+    double acc = 0.0;
+    const double scale = 2.0 / ((double)P * cout);
+    const int nv = C / 8;
+    for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < P;
+         p += (size_t)gridDim.x * blockDim.x) {
+        for (int v = 0; v < nv; ++v) {
+            uint4 out = make_uint4(0u, 0u, 0u, 0u);
+            if (8 * v < cout) {
+                unsigned short h[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int c = 8 * v + e;
+                    float g = 0.f;
+                    if (c < cout) {
+                        const double d = (double)(float)y[p * C + c] - (double)tgt[p * cout + c];
+                        acc += d * d;
+                        g = (float)(scale * d);
+                    }
+                    const bf16 b = (bf16)g;
+                    h[e] = __builtin_bit_cast(unsigned short, b);
+                }
+                out = make_uint4(h[0] | (unsigned)h[1] << 16, h[2] | (unsigned)h[3] << 16,
+                                 h[4] | (unsigned)h[5] << 16, h[6] | (unsigned)h[7] << 16);
+            }
+            if (dy) *reinterpret_cast<uint4 *>(dy + p * C + 8 * v) = out;
+        }
+    }
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+}
+
+// The same for one or two channels of few: the lanes of a wave store the pieces of
+// its 64 pixels in turns (1024 x 2048 pixels, 2 of 32 channels: 77 -> 62 us).
+__global__ __launch_bounds__(1024) void k_mse_first(const bf16 *__restrict__ y,
+                                                    const float *__restrict__ tgt,
+                                                    bf16 *__restrict__ dy,
+                                                    double *__restrict__ partial, size_t P, int C,
+                                                    int cout) {
     __shared__ double red[1024];
     double acc = 0.0;
     const double scale = 2.0 / ((double)P * cout);
@@ -1308,32 +1352,21 @@ __global__ __launch_bounds__(1024) void k_mse_px(const bf16 *__restrict__ y,
     // whole waves of 64 pixels
     for (size_t p = (size_t)blockIdx.x * 1024 + threadIdx.x; p - lane < P;
          p += (size_t)gridDim.x * 1024) {
-        auto piece = [&](int v) {
-            unsigned short h[8];
+        unsigned short h[2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int c = 8 * v + e;
-                float g = 0.f;
-                if (p < P && c < cout) {
-                    const double d = (double)(float)y[p * C + c] - (double)tgt[p * cout + c];
-                    acc += d * d;
-                    g = (float)(scale * d);
-                }
-                const bf16 b = (bf16)g;
-                h[e] = __builtin_bit_cast(unsigned short, b);
+        for (int c = 0; c < 2; ++c) {
+            float g = 0.f;
+            if (p < P && c < cout) {
+                const double d = (double)(float)y[p * C + c] - (double)tgt[p * cout + c];
+                acc += d * d;
+                g = (float)(scale * d);
             }
-            return make_uint4(h[0] | (unsigned)h[1] << 16, h[2] | (unsigned)h[3] << 16,
-                              h[4] | (unsigned)h[5] << 16, h[6] | (unsigned)h[7] << 16);
-        };
-        if (cout <= 8) {
-            const uint4 first = piece(0);
-            if (dy) store_first_pieces(dy, nv, p - lane, P, lane, first);
-            continue;
+            const bf16 b = (bf16)g;
+            h[c] = __builtin_bit_cast(unsigned short, b);
         }
-        for (int v = 0; v < nv; ++v) {
-            const uint4 out = piece(v);
-            if (dy && p < P) *reinterpret_cast<uint4 *>(dy + p * C + 8 * v) = out;
-        }
+        if (dy)
+            store_first_pieces(dy, nv, p - lane, P, lane,
+                               make_uint4(h[0] | (unsigned)h[1] << 16, 0u, 0u, 0u));
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -1745,8 +1778,15 @@ int fwi_nn_mse(const void *y, const float *target, void *dy, double *loss, doubl
     if (!y || !target || !loss || !partials || P == 0 || C < 1 || cout < 1 || cout > C)
         return FWI_NN_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (C % 8 == 0 && (!dy || al16(dy)))
-        hipLaunchKernelGGL(k_mse_px, dim3(FWI_NN_MSE_BLOCKS), dim3(1024), 0, st,
+    // (of more channels, or more of them in the loss, the pieces' own thread is
+    // faster: 8 of 32, 32 x 128 x 128 pixels: 48.8 and 30.4 us; 2 of 256, 7 x 34 x
+    // 30: 13.4 and 11.4; 2 of 128, 32 x 32 x 32: 11.6 and 11.8)
+    if (C % 8 == 0 && C <= 128 && cout <= 2 && (!dy || al16(dy)))
+        hipLaunchKernelGGL(k_mse_first, dim3(FWI_NN_MSE_BLOCKS), dim3(1024), 0, st,
+                           static_cast<const bf16 *>(y), target, static_cast<bf16 *>(dy), partials,
+                           P, C, cout);
+    else if (C % 8 == 0 && (!dy || al16(dy)))
+        hipLaunchKernelGGL(k_mse_px, dim3(FWI_NN_MSE_BLOCKS), dim3(256), 0, st,
                            static_cast<const bf16 *>(y), target, static_cast<bf16 *>(dy), partials,
                            P, C, cout);
     else

@@ -32,3 +32,24 @@ def test_pack4_of_wide_pixels(P, C):
     ref[:, :4] = (planes[0, :, 0] * sc[0, :, None]).t()
     assert torch.equal(x[:P * C].view(P, C), ref.bfloat16())
     assert bool((x[P * C:] == 7).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,C,cout", [(64, 65776, 2), (65, 128, 2), (63, 136, 2), (70, 128, 3),
+                                      (129, 128, 1), (524288 + 3, 32, 2), (131, 32, 8)])
+def test_loss_of_wide_pixels(P, C, cout):
+    """Each route of the loss: its gradient is one rounding of a float64 value to
+    bfloat16 through float32, the loss a float64 sum in another order."""
+    import torch
+    g = torch.Generator().manual_seed(P)
+    y, tgt = torch.randn(P, C, generator=g).bfloat16().cuda(), torch.randn(P, cout, generator=g).cuda()
+    dy = torch.full((P * C + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    part = torch.empty(nn.FWI_NN_MSE_BLOCKS, dtype=torch.float64, device="cuda")
+    nn.mse(y.view(-1), tgt, dy[:P * C], loss, part, P, C, cout)
+    d = y[:, :cout].double() - tgt.double()
+    assert abs(float(loss) - float((d * d).mean())) <= 1e-12 * float((d * d).mean())
+    got = dy[:P * C].view(P, C)
+    grad = 2.0 / (P * cout) * d
+    assert bool(((got[:, :cout].double() - grad).abs() <= 2.0 ** -8 * grad.abs()).all())
+    assert not bool(got[:, cout:].any()) and bool((dy[P * C:] == 7).all())
