@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "fwi_nn.h"
+#include "fwi_nn_route.h"
 
 namespace {
 
@@ -435,51 +436,21 @@ __global__ __launch_bounds__(256) void k_conv3x3_rows(const bf16 *__restrict__ x
     }
 }
 
-// Bands of rows per image for `base` strips and channel groups: a block pays
-// about 6 rows' time for its weights and first rows and reads 2 halo rows; with
-// one block per CU nothing hides its latencies (weighed 1.3), two share a CU, and
-// of a last, partial round beyond that half the idle time counts.  Fitted to
-// sweeps of the block count over the network's layers: 32 images of 128 x 128,
-// 32 channels, best at 512 blocks (18.6 us; 256: 22.4, 1024: 20.8), of 32 x 32,
-// 64 to 128 channels, at 256 (13.2; 512: 14.8, 1024: 20.8).
-int row_bands(long long base, int H) {
-    int best = 1;
-    double best_t = 1e300;
-    for (int nb = 1; nb <= H && (nb == 1 || base * nb <= 4096); ++nb) {
-        const int rows = (H + nb - 1) / nb;
-        const double r = (double)(base * nb) / 256.0, up = std::ceil(r);
-        const double rounds = r <= 1.0 ? 1.3 : (r <= 2.0 ? up : r + 0.5 * (up - r));
-        const double t = (rows + 2) * rounds + 6.0 * std::ceil(r / 2.0);
-        if (t < best_t) {
-            best_t = t;
-            best = nb;
-        }
-    }
-    return best;
-}
-
-// Share of the 16-pixel tiles of an image row that is image, in strips of at most
-// bw pixels.
-double row_use(int W, int bw) {
-    const int nstrip = (W + bw - 1) / bw, strip = (W + nstrip - 1) / nstrip;
-    return (double)W / (nstrip * ((strip + 15) / 16 * 16));
-}
-
 template <int CI, int CT, int CG, int PG>
 hipError_t launch_rows(const bf16 *x, const bf16 *w, const float *bias, const bf16 *mask, bf16 *y,
-                       int N, int H, int W, int Co, int relu, bool kxc, hipStream_t st) {
-    constexpr int BW = 4096 / CI;
-    const int nstrip = (W + BW - 1) / BW, strip = (W + nstrip - 1) / nstrip;
-    const int nco = Co / (16 * CT * CG);
-    const int bands = row_bands((long long)N * nstrip * nco, H);
-    const int rows = (H + bands - 1) / bands, nrow = (H + rows - 1) / rows;
-    const dim3 grid((unsigned)(N * nrow * nstrip), (unsigned)nco);
-    auto kernel = kxc ? (mask ? k_conv3x3_rows<CI, CT, CG, PG, true, true>
-                              : k_conv3x3_rows<CI, CT, CG, PG, true, false>)
-                      : (mask ? k_conv3x3_rows<CI, CT, CG, PG, false, true>
-                              : k_conv3x3_rows<CI, CT, CG, PG, false, false>);
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, x, w, bias, mask, y, H, W, Co, relu, strip,
-                       nstrip, rows, nrow);
+                       int N, int H, int W, int Co, int relu, const fwi_nn::ConvRoute &route,
+                       hipStream_t st) {
+    const fwi_nn::RowsPlan &p = route.rows;
+    if (p.ct != CT || p.cg != CG || p.pg != PG) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(N * p.nrow * p.nstrip), (unsigned)p.nco);
+    // 32 channels: one order
+    constexpr bool two = CI > 32;
+    auto kernel = route.kxc && two ? (mask ? k_conv3x3_rows<CI, CT, CG, PG, two, true>
+                                           : k_conv3x3_rows<CI, CT, CG, PG, two, false>)
+                                   : (mask ? k_conv3x3_rows<CI, CT, CG, PG, false, true>
+                                           : k_conv3x3_rows<CI, CT, CG, PG, false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, x, w, bias, mask, y, H, W, Co, relu, p.strip,
+                       p.nstrip, p.rows, p.nrow);
     return hipGetLastError();
 }
 
@@ -1490,40 +1461,24 @@ int conv3x3(const void *x, const void *w, const float *bias, const void *mask, v
     const bf16 *wb = static_cast<const bf16 *>(w);
     const bf16 *mb = static_cast<const bf16 *>(mask);
     bf16 *yb = static_cast<bf16 *>(y);
-    // LDS-tiled kernel when it still gives the chip enough blocks, with the
-    // narrower channel tile where only that one does, and 64-pixel blocks
-    // where 128-pixel blocks would leave fewer than two blocks per CU
-    int bn = Co % 64 == 0 ? 64 : 32;
-    if (bn == 64 && (P + 127) / 128 * (Co / 64) < 256) bn = 32;
-    const int64_t lds_blocks = (P + 127) / 128 * (Co / bn);
-    // Row-marching kernel for 32, 64 and 128 input channels where y allows its
-    // 8-byte stores: always in place of the smallest layers' kernel (128 -> 64
-    // channels, 3 images of 45 x 83: 26.6 -> 9.5 us), and in place of the
-    // LDS-tiled one unless its 16-pixel tiles pad the rows too much (20 images
-    // of 100 x 17, 128 channels: 26.8 -> 31.5 us, of 144 columns 30.2 -> 32.0;
-    // 32 of 70 x 18, 64 channels: 12.9 -> 18.3) or there is too little to win
-    // against its start (64 -> 32 channels, 32 images of 18 x 130: 12.8 -> 14.3)
-    const bool kxc = lds_blocks < 256;
-    if ((Ci <= 64 || Ci == 128) && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(mask)) & 7) == 0 &&
-        (kxc || (row_use(W, 4096 / Ci) >= (Ci == 128 ? 0.92 : 0.8) &&
-                 !(Ci == 64 && Co == 32 && P < 1 << 17)))) {
-        hipError_t e;
-        if (Ci == 32)
-            e = Co % 64 == 0 ? launch_rows<32, 2, 2, 2>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st)
-                             : launch_rows<32, 2, 1, 4>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
-        else if (Ci == 128)
-            e = Co % 64 == 0 ? launch_rows<128, 1, 4, 1>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st)
-                             : launch_rows<128, 1, 2, 2>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
-        else if (Co % 128 == 0)
-            e = launch_rows<64, 2, 4, 1>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
-        else
-            e = Co % 64 == 0 ? launch_rows<64, 2, 2, 2>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st)
-                             : launch_rows<64, 2, 1, 4>(xb, wb, bias, mb, yb, N, H, W, Co, relu, kxc, st);
-        return status(e);
+    const bool aligned8 =
+        ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(mask)) & 7) == 0;
+    const fwi_nn::ConvRoute route = fwi_nn::conv_route(N, H, W, Ci, Co, aligned8);
+    if (route.kernel == fwi_nn::ConvRoute::Rows) {
+        auto run = [&](auto f) { return f(xb, wb, bias, mb, yb, N, H, W, Co, relu, route, st); };
+        const bool co64 = Co % 64 == 0;
+        if (Ci == 32) return status(run(co64 ? launch_rows<32, 2, 2, 2> : launch_rows<32, 2, 1, 4>));
+        if (Ci == 128)
+            return status(run(co64 ? launch_rows<128, 1, 4, 1> : launch_rows<128, 1, 2, 2>));
+        if (Co % 128 == 0) return status(run(launch_rows<64, 2, 4, 1>));
+        return status(run(co64 ? launch_rows<64, 2, 2, 2> : launch_rows<64, 2, 1, 4>));
     }
-    if (lds_blocks >= 256) {
-        // (the 64-pixel tile below 1024 blocks of 128 made the network's
-        // 32 x 32-pixel layers slower)
+    if (route.kernel == fwi_nn::ConvRoute::Lds) {
+        // 64-pixel blocks where 128-pixel blocks would leave fewer than two blocks
+        // per CU (below 1024 blocks of 128 they made the network's 32 x 32-pixel
+        // layers slower)
+        const int bn = route.bn;
+        const int64_t lds_blocks = (P + 127) / 128 * (Co / bn);
         const int bm = lds_blocks < 512 ? 64 : 128;
         const dim3 grid((unsigned)((P + bm - 1) / bm), (unsigned)(Co / bn));
         // (the mask's test at run time cost the calls without one 3 to 5%)
