@@ -673,22 +673,24 @@ __global__ __launch_bounds__(256) void k_wgrad(const bf16 *__restrict__ x,
     if (do_bias && t < 32) o[tile + cot * 32 + t] = bsum;
 }
 
-// The same gradients for images of 128 pixels and more, marching down the rows of strips of at most BW pixels as
-// the row convolution does: input rows pass once through a ring in LDS (one
-// pixel of halo, zeros outside the image), output-gradient rows through another.
-// A block owns 32 x 32 channels for all nine taps; each of its NW waves keeps all
-// of them (36 sums of 16 x 16 in registers), so a fragment read from LDS serves
-// several products, and the waves take turns at the pixels.  The reduction index
-// of a product is 32 pixels: four groups of 8 neighbouring pixels of a row, which
-// may lie in different rows, so narrow images keep the matrix cores as busy as
-// wide ones (rows are padded to 8 pixels with zero gradients).  A lane reads 12
-// pixels of one channel by three transposing reads and shifts the fragments of
-// the three kx taps out of them.  Block b takes the steps (strips of the images,
-// srow rows at a time) [b T / G, (b + 1) T / G) and writes one record of sums.
-// The accumulators leave two waves per SIMD, so a step's loads (issued one step
-// ahead) are what it waits for, about 1.8 us for 0.6 us of products and LDS reads;
-// loads two steps ahead, or half the sums per wave and four waves, spill registers
-// (41 and 54 us against 31 for 32 x 128 x 128 pixels, 32 -> 32 channels).
+// The same gradients where images fill its steps (fwi_nn_route.h), marching down the
+// rows of strips of at most BW pixels as the row convolution does: input rows pass
+// once through a ring in LDS (one pixel of halo, zeros outside the image),
+// output-gradient rows through another.  A block owns 32 x 32 channels for all nine
+// taps; each of its NW waves keeps all of them (36 sums of 16 x 16 in registers), so a
+// fragment read from LDS serves several products, and the waves take turns at the
+// pixels.  The reduction index of a product is 32 pixels: four groups of 8
+// neighbouring pixels of a row, which may lie in different rows, so the matrix cores
+// work on images of eight columns as on wide ones (rows are padded to 8 pixels with
+// zero gradients).  A lane reads 12 pixels of one channel by three transposing reads
+// and shifts the fragments of the three kx taps out of them.  Block b takes the steps
+// (strips of the images, srow rows at a time) [b T / G, (b + 1) T / G) and writes one
+// record of sums.  The accumulators leave two waves per SIMD and take the registers to
+// their end (256, with 4 values of the staging spilled, 20 bytes of scratch per lane),
+// so a step's loads (issued one step ahead) are what it waits for, about 1.8 us for
+// 0.6 us of products and LDS reads; loads two steps ahead (62 spilled), or half the
+// sums per wave and four waves, are slower (41 and 54 us against 31 for 32 x 128 x 128
+// pixels, 32 -> 32 channels).
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // records: 4-byte aligned
 constexpr int kWRP = 40;    // pitch of a pixel in LDS: 32 channels + 8 padding
 
@@ -920,33 +922,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_wgrad_rows(
         for (int w2 = 1; w2 < NW; ++w2) v += red[w2 * 32 + t];
         out[tile + cot + t] = v;
     }
-}
-
-// Strips and rows per step of k_wgrad_rows: the pair with the fewest steps (of
-// at most BW pixels each), the widest strips among equals (least halo).
-struct WgradPlan {
-    int strip, nstrip, srow;
-    long long steps;
-};
-
-template <int BW>
-WgradPlan wgrad_plan(int N, int H, int W) {
-    WgradPlan best{};
-    const int least = (W + BW - 1) / BW;
-    for (int n = least; n <= least + 8; ++n) {
-        const int strip = n == 1 ? W : ((W + n - 1) / n + 7) / 8 * 8;
-        const int strip8 = (strip + 7) / 8 * 8;
-        const int ns = (W + strip - 1) / strip, srow = std::min(BW / strip8, H);
-        const long long steps = (long long)N * ns * ((H + srow - 1) / srow);
-        if (best.steps == 0 || steps < best.steps) best = {strip, ns, srow, steps};
-        if (strip8 <= 16) break;
-    }
-    return best;
-}
-
-// records of sums: at most `nsplit`, one per step, and `fill` blocks
-int wgrad_blocks(int nsplit, long long steps, int fill) {
-    return (int)std::min<long long>({(long long)nsplit, steps, (long long)std::max(1, fill)});
 }
 
 // sum_k part[k][i] over the nsplit records of n = n1 + n2 floats, written
@@ -1599,33 +1574,20 @@ int fwi_nn_wgrad(const void *x, const void *dz, float *dw, float *db, int32_t N,
     hipStream_t st = static_cast<hipStream_t>(stream);
     float *part = static_cast<float *>(ws);
     const int tiles = (Co / 32) * (Ci / 32);
-    // As many blocks as the chip holds at once, one of eight waves per CU or two
-    // of four.  Eight waves write half the records: with up to 8 steps per block
-    // (3 x 45 x 83, 64 -> 128: 17.9 us against 22.1 with four; 32 x 128 x 128, 32
-    // channels: 30.3, 31.7).  Beyond, two blocks that wait for each other's loads
-    // (1024 x 2048, 32 channels: 83.7 against 79.0; 512 x 1024, 64: 76.2, 68.2).
-    // Images below 128 pixels leave a step's pixels mostly padding and start a
-    // strip each step: the flattened form (512 x 8 x 8, 128 channels: 44.6 us
-    // against 47.2; 1024 x 1 x 1, 64 channels: 12.8, 64.1); from 32 x 13 x 14 on,
-    // 64 -> 32 channels, the rows win (12.6 against 14.7; 32 x 16 x 16, 256
-    // channels: 33.3, 44.4).
-    const WgradPlan p8 = wgrad_plan<256>(N, H, W), p4 = wgrad_plan<128>(N, H, W);
-    const int g8 = wgrad_blocks(nsplit, p8.steps, 256 / tiles);
-    if (H * W < 128) {
+    const fwi_nn::WgradRoute r = fwi_nn::wgrad_route(N, H, W, Ci, Co, nsplit);
+    nsplit = r.records;
+    if (r.waves == 0)
         hipLaunchKernelGGL(k_wgrad<kWgradChunk>, dim3(nsplit, tiles), dim3(256), 0, st,
                            static_cast<const bf16 *>(x), static_cast<const bf16 *>(dz), part, N, H,
                            W, Ci, Co);
-    } else if (p8.steps <= 8LL * g8) {
-        nsplit = g8;
+    else if (r.waves == 8)
         hipLaunchKernelGGL(k_wgrad_rows<8>, dim3(nsplit, tiles), dim3(512), 0, st,
                            static_cast<const bf16 *>(x), static_cast<const bf16 *>(dz), part, N, H,
-                           W, Ci, Co, p8.strip, p8.nstrip, p8.srow);
-    } else {
-        nsplit = wgrad_blocks(nsplit, p4.steps, 512 / tiles);
+                           W, Ci, Co, r.plan.strip, r.plan.nstrip, r.plan.srow);
+    else
         hipLaunchKernelGGL(k_wgrad_rows<4>, dim3(nsplit, tiles), dim3(256), 0, st,
                            static_cast<const bf16 *>(x), static_cast<const bf16 *>(dz), part, N, H,
-                           W, Ci, Co, p4.strip, p4.nstrip, p4.srow);
-    }
+                           W, Ci, Co, r.plan.strip, r.plan.nstrip, r.plan.srow);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return FWI_NN_EHIP;
     const size_t nw = (size_t)Co * 9 * Ci, n = nw + Co;

@@ -1,5 +1,5 @@
-// Which kernel a 3x3 convolution takes (fwi_nn.hip), and how the row-marching one
-// splits its images.  Host code without a GPU type in it, so that the rule can be
+// Which kernel a 3x3 convolution and its weight gradient take (fwi_nn.hip), and how
+// the row-marching ones split their images.  Host code without a GPU type in it, so that the rule can be
 // checked on the CPU.
 #pragma once
 
@@ -134,6 +134,76 @@ inline ConvRoute conv_route(int N, int H, int W, int Ci, int Co, bool aligned8) 
     // (a launch holds fewer than 2^32 threads)
     if (c.rows.blocks < 1 << 24 && rows_time(c.rows, Ci, Co) < most) c.kernel = ConvRoute::Rows;
     return c;
+}
+
+// Strips and rows per step of k_wgrad_rows: the pair with the fewest steps (of
+// at most BW pixels each), the widest strips among equals (least halo).
+struct WgradPlan {
+    int strip, nstrip, srow;
+    long long steps;
+};
+
+inline WgradPlan wgrad_plan(int BW, int N, int H, int W) {
+    WgradPlan best{};
+    const int least = (W + BW - 1) / BW;
+    for (int n = least; n <= least + 8; ++n) {
+        const int strip = n == 1 ? W : ((W + n - 1) / n + 7) / 8 * 8;
+        const int strip8 = (strip + 7) / 8 * 8;
+        const int ns = (W + strip - 1) / strip, srow = std::min(BW / strip8, H);
+        const long long steps = (long long)N * ns * ((H + srow - 1) / srow);
+        if (best.steps == 0 || steps < best.steps) best = {strip, ns, srow, steps};
+        if (strip8 <= 16) break;
+    }
+    return best;
+}
+
+// Rows: as many blocks as the chip holds at once, one of eight waves per CU or two
+// of four (at most one per step and record).  Eight waves write half the records:
+// with up to 8 steps per block (3 x 45 x 83, 64 -> 128: 17.9 us against 22.1 with
+// four; 32 x 128 x 128, 32 channels: 30.3, 31.7).  Beyond, two blocks that wait for
+// each other's loads (1024 x 2048, 32 channels: 83.7 against 79.0; 512 x 1024, 64:
+// 76.2, 68.2).
+struct WgradRoute {
+    int waves;              // of the row-marching kernel, 0: the flattened one
+    int records;            // partial sums written
+    WgradPlan plan;
+};
+
+// Rows or the flattened kernel, by the time of each, in us: both write and read
+// their records (37.7 MB of them: 16 us), the flattened one takes its chunks of 32
+// pixels in any shape, the rows take steps of 256 (eight waves) or 128 pixels, of
+// which a narrow image fills an eighth per column, and pay for each strip's start.
+// Constants from 40 shapes x 7 channel counts, within 15% of nearly all.  Images of
+// 32 x 16 x 16, 256 channels: rows 33.3, flattened 44.4; 700 of 13 x 14: 337, 437; but
+// 8192 x 1, 256 channels: 103, 44; 512 of 128 x 2: 757, 449; 1000 of 12 x 11, 64
+// channels: 43.3, 40.7.  Below 128 pixels an image leaves a step mostly padding (512 x
+// 8 x 8, 128 channels: 47.2, 44.6; 1024 x 1 x 1, 64 channels: 64.1, 12.8).
+inline WgradRoute wgrad_route(int N, int H, int W, int Ci, int Co, int nsplit) {
+    const int tiles = (Co / 32) * (Ci / 32);
+    WgradRoute flat{0, nsplit, {}};
+    if (H * W < 128) return flat;
+    auto blocks = [&](long long steps, int fill) {
+        return (int)std::min<long long>({(long long)nsplit, steps, (long long)std::max(1, fill)});
+    };
+    const double work = (double)N * H * W * tiles;
+    auto share = [&](int records) { return records * 36.0 * Ci * Co / 37.7e6; };
+    const double f = share(nsplit), busy = std::max(1.0, 512.0 / ((double)nsplit * tiles));
+    const double flat_time =
+        std::max(std::max(11.5, 8 + 16 * f), 6 + 12 * f + 4.9e-5 * work * busy);
+    WgradRoute r{8, 0, wgrad_plan(256, N, H, W)};
+    r.records = blocks(r.plan.steps, 256 / tiles);
+    double step = 1.7, start = 0.3, record = 16;
+    if (r.plan.steps > 8LL * r.records) {
+        r = {4, 0, wgrad_plan(128, N, H, W)};
+        r.records = blocks(r.plan.steps, 512 / tiles);
+        step = 1.35, start = 0.9, record = 8;
+    }
+    const int per = (H + r.plan.srow - 1) / r.plan.srow;
+    const double each = std::ceil((double)r.plan.steps / r.records);
+    // (more tiles than the chip holds blocks: rounds of them)
+    const double rounds = std::max(1.0, (double)r.records * tiles / (r.waves == 8 ? 256 : 512));
+    const double time = 10 + record * share(r.records) + rounds * each * (step + start / per);
+    return time < 0.94 * flat_time ? r : flat;
 }
 
 }  // namespace fwi_nn

@@ -1,5 +1,5 @@
-"""The rule that picks a convolution's kernel (csrc/fwi_nn_route.h), compiled by the
-host compiler: the row-marching kernel for the network's layers, not for images of a
+"""The rules that pick the kernel of a convolution and of its weight gradient
+(csrc/fwi_nn_route.h), compiled by the host compiler: the row-marching kernel for the network's layers, not for images of a
 few rows or columns (where it starts a block per image and was up to thirty times
 slower), never with more threads than a launch holds, and with a split that covers
 the image; the shapes that tests/test_gpu_nn_route.py runs take the kernel they are
@@ -21,6 +21,11 @@ extern "C" void route(int N, int H, int W, int Ci, int Co, int aligned, long lon
     o[5] = c.rows.rows; o[6] = c.rows.nrow; o[7] = c.rows.nco; o[8] = c.rows.blocks;
     o[9] = c.rows.ct; o[10] = c.rows.cg; o[11] = c.rows.pg;
 }
+extern "C" void wgrad(int N, int H, int W, int Ci, int Co, int nsplit, long long *o) {
+    const fwi_nn::WgradRoute r = fwi_nn::wgrad_route(N, H, W, Ci, Co, nsplit);
+    o[0] = r.waves; o[1] = r.records; o[2] = r.plan.strip; o[3] = r.plan.nstrip;
+    o[4] = r.plan.srow; o[5] = r.plan.steps;
+}
 """
 ROWS, LDS, DIRECT = 0, 1, 2
 
@@ -34,7 +39,7 @@ EDGES = [(300, 20, 31, 32, 64), (8, 257, 128, 32, 32), (4, 500, 129, 32, 32), (4
 
 
 @pytest.fixture(scope="module")
-def route(tmp_path_factory):
+def lib(tmp_path_factory):
     cxx = shutil.which("g++")
     if cxx is None:
         pytest.skip("no host compiler")
@@ -43,8 +48,11 @@ def route(tmp_path_factory):
     src.write_text(CODE)
     subprocess.run([cxx, "-std=c++17", "-O2", "-Wall", "-fPIC", "-shared", "-I", CSRC, str(src),
                     "-o", str(so)], check=True)
-    lib = ctypes.CDLL(str(so))
+    return ctypes.CDLL(str(so))
 
+
+@pytest.fixture(scope="module")
+def route(lib):
     def f(N, H, W, Ci, Co, aligned=1):
         o = (ctypes.c_longlong * 12)()
         lib.route(N, H, W, Ci, Co, aligned, o)
@@ -90,3 +98,41 @@ def test_the_edge_shapes_take_the_row_kernel(route):
     got = {s: route(*s) for s in EDGES}
     assert [s for s in EDGES if got[s][0] != ROWS] == []
     assert {got[s][2] for s in EDGES} == {0, 1}   # both orders of the reduction
+
+
+def _nsplit(N, H, W, Ci, Co):
+    """as the network chooses it"""
+    return max(1, min(-(-N * H * W // 32), -(-1024 // (Co // 32 * (Ci // 32))), 1024))
+
+
+@pytest.fixture(scope="module")
+def wgrad(lib):
+    def f(N, H, W, Ci, Co, nsplit=None):
+        o = (ctypes.c_longlong * 6)()
+        lib.wgrad(N, H, W, Ci, Co, nsplit or _nsplit(N, H, W, Ci, Co), o)
+        return list(o)
+    return f
+
+
+@pytest.mark.parametrize("shape,rows", [
+    # one to three columns fill at most three eighths of a step
+    ((1, 8192, 1, 256, 256), 0), ((1, 32768, 2, 128, 128), 0), ((512, 128, 2, 64, 64), 0),
+    ((512, 128, 1, 128, 256), 0), ((64, 64, 2, 256, 256), 0), ((64, 130, 1, 32, 32), 0),
+    ((64, 1, 130, 256, 256), 0), ((1000, 12, 11, 128, 64), 0), ((512, 8, 8, 128, 128), 0),
+    # the network's layers, and narrow ones that gain all the same
+    ((32, 128, 128, 32, 32), 1), ((32, 64, 64, 64, 64), 1), ((32, 32, 32, 128, 128), 1),
+    ((32, 16, 16, 256, 256), 1), ((3, 45, 83, 64, 128), 1), ((1, 1024, 2048, 32, 32), 1),
+    ((700, 13, 14, 256, 256), 1), ((64, 64, 4, 64, 64), 1), ((1, 8192, 8, 128, 128), 1)])
+def test_weight_gradients_of_narrow_images_stay_flattened(wgrad, shape, rows):
+    assert (wgrad(*shape)[0] > 0) == bool(rows)
+
+
+def test_weight_gradient_splits_cover_the_image(wgrad):
+    for N, H, W in [(n, h, w) for n in (1, 5) for h in (1, 2, 33, 500) for w in (1, 7, 130, 257, 3000)]:
+        for ci, co, ns in ((32, 32, None), (128, 256, None), (32, 32, 1), (64, 64, 7), (1024, 1024, 3)):
+            waves, records, strip, nstrip, srow, steps = wgrad(N, H, W, ci, co, ns)
+            assert waves in (0, 4, 8) and 1 <= records <= (ns or _nsplit(N, H, W, ci, co))
+            if waves:
+                assert (nstrip - 1) * strip < W <= nstrip * strip and 1 <= srow <= H
+                assert srow * (-(-strip // 8) * 8) <= 32 * waves
+                assert records <= steps == N * nstrip * -(-H // srow)
