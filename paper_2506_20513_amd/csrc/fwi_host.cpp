@@ -194,10 +194,10 @@ void set_streams(Layout &L, int groups) {
     L.naband = pick_bands(L.d, K, L.nstrip, adj_waves(K), L.abands, groups);
 }
 
-// The layout's decomposition, one of `groups` launches of its kind that share
-// the chip.
-void make_tiling(const Dims &d, Layout &L, int groups) {
-    const long long cells = (long long)groups * d.S * d.NX * d.NY, tiles = groups * tile_count(d);
+// The decomposition of a layout with the shots of `all`, or of one of the `groups`
+// that they run in side by side: every group of a call makes the call's choice.
+void make_tiling(const Dims &all, Layout &L, int groups) {
+    const long long cells = (long long)all.S * all.NX * all.NY, tiles = tile_count(all);
     if (use_tiles(L.depth, cells, tiles))
         set_tiles(L, pick_tile(tiles));
     else
@@ -353,7 +353,7 @@ int make_group_layout(const Dims &d, int G, GroupLayout &GL) {
         dg.S = GL.s0[g + 1] - GL.s0[g];
         const int rc = make_layout(dg, -1, GL.grp[g], 0, 0, off, &sh, GL.s0[g]);
         if (rc != FWI_OK) return rc;
-        make_tiling(dg, GL.grp[g], G);
+        make_tiling(d, GL.grp[g], G);
         off = GL.grp[g].total;
     }
     sh.total = off;

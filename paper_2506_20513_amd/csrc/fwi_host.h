@@ -18,9 +18,9 @@ int make_dims(const fwi_grid *grid, const fwi_geom *geom, Dims &d);
 // Checkpoint interval minimising checkpoint plus segment-buffer memory.
 int stream_depth(const Dims &d);
 int choose_k(const Dims &d, int depth);
-// The decomposition of the stencil passes (stored in L): tiles or streams;
-// `groups` shot groups share the chip.
-void make_tiling(const Dims &d, Layout &L, int groups = 1);
+// The decomposition of the stencil passes (stored in L): tiles or streams, by the
+// shots of the whole call (`all`), of which `groups` share the chip.
+void make_tiling(const Dims &all, Layout &L, int groups = 1);
 // Whether that many cells (all shots) run on tiles; a problem's tiles of the
 // large height; the height for that many tiles in flight; tiles of height
 // `rows` for both kernels; the streaming decomposition.
