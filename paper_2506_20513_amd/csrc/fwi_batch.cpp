@@ -81,23 +81,29 @@ hipError_t ok(int rc) { return rc == FWI_OK ? hipSuccess : hipErrorUnknown; }
 
 // Temporal depth of the passes and row bands of height `rows`.  0: tiles of
 // one height for all problems (their passes share launches), the imaging sums
-// grouped by `depth`, or at depth 8 for a batch too large for them the streaming
-// default of each problem.  At depth 4 tiles are faster for any batch: 12, 24 and
-// 48 models of 200 x 100 to 640 x 320, 8 shots: 504, 848, 1556 ms with streams,
-// 268, 562, 1121 with tiles (the merged launches read their arguments from a
-// table, which costs the streaming kernels registers).  The checkpoint interval
-// is a multiple of both depths, so the workspace layout does not change.
+// grouped by `depth`, or the streaming default of each problem: at depth 8 by the line
+// of a single call, at depth 4 only for many grids of about one strip of columns.  (The
+// merged launches read their arguments from a table, which costs the streaming kernels
+// registers.  Streams, tiles in ms, 96 steps, 8 shots unless named: 400 models of 56 x
+// 56 42.2, 47.7, 100 of them 11.7, 12.0; 400 of 60 x 60 60.1, 47.9, of 100 x 100 85.4,
+// 82.2; 96 of 148 x 148 35.5, 29.4; 16 of 552 x 296, 24 shots, 64.0, 59.7; 8 of 1040 x
+// 640 40.2, 34.4; 2 of 1040 x 2088, 16 shots, 63.3, 52.6; one of 2088 x 1064, 24 shots,
+// 54.7, 43.3.)  The checkpoint interval is a multiple of both depths, so the workspace
+// layout does not change.
 void set_tiling(std::vector<Problem> &probs, int depth, int rows) {
-    long long tiles = 0, cells = 0;
+    long long tiles = 0, cells = 0, lanes = 0;
     for (const Problem &p : probs) {
         tiles += tile_count(p.d);
         cells += (long long)p.d.S * p.d.NX * p.d.NY;
+        lanes += lane_cells(p.d, depth);
     }
+    const bool tiled = depth == kDepthSmall ? tiles <= 4096 || lanes >= 1000 * tiles
+                                            : use_tiles(depth, false, cells, lanes, tiles);
     for (Problem &p : probs) {
         p.L.depth = depth;
         if (rows > 0)
             fixed_bands(p.L, rows, depth);
-        else if (depth == kDepthSmall || use_tiles(depth, cells, tiles))
+        else if (tiled)
             set_tiles(p.L, pick_tile(tiles));
         else
             set_streams(p.L);

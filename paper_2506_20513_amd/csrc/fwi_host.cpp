@@ -142,24 +142,44 @@ constexpr double kFwdWaves = 4.0;
 double adj_waves(int depth) { return depth == kDepthLarge ? 3.0 : 4.0; }
 
 // Tiles or streams.  The streaming kernels read a field row once per pass and
-// pay a load latency per row; the tile kernels read a tile with its halo (1.8
-// times its cells) at once and keep up to 48 x 48 cells of it.  On a chip not full
-// of waves tiles are faster, up to 15 M cells (all shots of the call) against
-// depth 8 and 7 M against depth 4: one gradient took (streams, tiles; ms)
-//   2088 x 1064, 96 steps   4 shots (9 M) 8.5, 7.9    6 (13 M) 12.1, 11.7
-//                           8 (18 M) 14.8, 15.5      16 (36 M) 23.0, 28.9
-//   552 x 296, 192 steps   24 shots (4 M) 9.7, 8.4   40 (6.5 M) 14.0, 13.8
-//   552 x 296, 96 steps    48 (8 M) 8.5, 9.1         96 (16 M) 15.6, 17.7
-// Beyond, 96 steps take 1.9 to 2.0 us per tile and at depth 4 0.9 to 1.0 ns per
-// cell, so against depth 4 it depends on how the grid fits its tiles: from 2050
-// cells per tile on (in brackets)
-//   1040 x 640, 96 steps (2161)    40 shots (27 M) 23.7, 23.3   56 33.6, 32.3
-//   480 x 480, 192 steps (2304)    48 (11 M) 20.3, 18.7
-//   740 x 540, 96 steps (2081)     24 (10 M) 9.6, 9.3     48 18.0, 18.2
-//   640 x 340, 192 steps (1943)    48 (10 M) 19.6, 21.1
-bool use_tiles(int depth, long long cells, long long tiles) {
-    if (depth == kDepthLarge) return cells <= 15LL << 20;
-    return cells <= 7LL << 20 || cells >= 2050 * tiles;
+// pay a load latency per row, which only more waves than the chip holds hide; the tile
+// kernels read a tile with its halo (1.8 times its cells) at once and keep up to 48 x
+// 48 cells of it, fewer where the grid fits its tiles badly (`per`).  So few tiles are
+// faster whatever the fit, and many only with a good one.  One call of 96 steps
+// (streams, tiles; ms), traces only and gradient:
+//                     cells per tile   traces        gradient
+//   56 x 56, 300 shots            784   1.31  1.20     3.97  4.07
+//   100 x 100, 100 shots         1111   1.20  0.86     3.73  3.08
+//     200 / 600                         1.44  1.39     4.30  5.18 /  8.38 14.30
+//   148 x 148, 100 / 300         1369   1.33  1.18     4.17  4.37 /  7.99 11.71
+//   552 x 296, 24 / 48           1945   1.31  1.12     4.89  4.48 /  7.65  8.34
+//   740 x 540, 24                2081   2.04  2.25     8.86  8.97
+//   1000 x 1000, 12              2268   2.71  2.25    11.33  9.96
+// against depth 4: per 96 steps, 2.45 us per tile of a gradient and 0.9 ns per cell plus
+// 2.15 ms of latency for streams, 0.58, 0.2 and 0.8 traces only, and from a fit of 2050
+// (2200) cells tiles however many; traces only, tiles of a lesser fit up to 3500 of
+// them (740 x 540, 20 shots: 1.85, 1.93).
+//
+// At depth 8 (grids of 2^20 cells and more) up to 4000 tiles, and beyond by the share of
+// the streams' lanes that is grid (`lanes`: their cells, pairs of strips padded):
+//   1160 x 920, 8 / 14 shots     2134   2.52  1.85    10.49  7.70 / 12.31 13.32
+//   2088 x 1064, 4 / 6 / 8       2195   2.04  1.80     7.97  7.57 / 11.03 11.27 / 13.50 14.99
+//   4000 x 300, 8 / 12           2041   2.29  2.39     8.96  9.40 / 11.57 13.84
+//   300 x 4000, 12               2041   3.64  3.21    15.48 13.12
+bool use_tiles(int depth, bool traces_only, long long cells, long long lanes, long long tiles) {
+    const double t = (double)tiles, per = (double)cells / t, wide = (double)lanes / t;
+    if (depth == kDepthLarge)
+        return tiles <= 4000 || (tiles <= 5800 && wide >= 2150) || (tiles <= 8000 && wide >= 2400);
+    const double kc = (double)cells * 1e-3;
+    if (traces_only) return per >= 2200 || (tiles <= 3500 && 0.58 * t - 0.2 * kc < 800);
+    return per >= 2050 || 2.45 * t - 0.9 * kc < 2150;
+}
+
+// Cells of the streaming strips, a pair of strips per workgroup at depth 8.
+long long lane_cells(const Dims &d, int depth) {
+    const int OW = 64 - 2 * depth, pair = depth == kDepthLarge ? 2 : 1;
+    const long long strips = (d.NX + OW - 1) / OW, even = (strips + pair - 1) / pair * pair;
+    return even * OW * d.NY * d.S;
 }
 
 long long tile_count(const Dims &d) {
@@ -198,7 +218,7 @@ void set_streams(Layout &L, int groups) {
 // that they run in side by side: every group of a call makes the call's choice.
 void make_tiling(const Dims &all, Layout &L, int groups) {
     const long long cells = (long long)all.S * all.NX * all.NY, tiles = tile_count(all);
-    if (use_tiles(L.depth, cells, tiles))
+    if (use_tiles(L.depth, L.mode == FWI_SAVE_NONE, cells, lane_cells(all, L.depth), tiles))
         set_tiles(L, pick_tile(tiles));
     else
         set_streams(L, groups);

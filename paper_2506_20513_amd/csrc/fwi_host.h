@@ -21,10 +21,12 @@ int choose_k(const Dims &d, int depth);
 // The decomposition of the stencil passes (stored in L): tiles or streams, by the
 // shots of the whole call (`all`), of which `groups` share the chip.
 void make_tiling(const Dims &all, Layout &L, int groups = 1);
-// Whether that many cells (all shots) run on tiles; a problem's tiles of the
-// large height; the height for that many tiles in flight; tiles of height
-// `rows` for both kernels; the streaming decomposition.
-bool use_tiles(int depth, long long cells, long long tiles);
+// Whether a call of that many cells, streaming lanes' cells and tiles of the large
+// height (over all shots) runs on tiles; a problem's such lanes' cells and tiles; the
+// height for that many tiles in flight; tiles of height `rows` for both kernels; the
+// streaming decomposition.
+bool use_tiles(int depth, bool traces_only, long long cells, long long lanes, long long tiles);
+long long lane_cells(const Dims &d, int depth);
 long long tile_count(const Dims &d);
 int pick_tile(long long tiles);
 void set_tiles(Layout &L, int rows);
