@@ -91,16 +91,18 @@ hipError_t ok(int rc) { return rc == FWI_OK ? hipSuccess : hipErrorUnknown; }
 // 54.7, 43.3.)  The checkpoint interval is a multiple of both depths, so the workspace
 // layout does not change.
 void set_tiling(std::vector<Problem> &probs, int depth, int rows) {
-    long long tiles = 0, cells = 0, lanes = 0;
+    long long tiles = 0, cells = 0, lanes = 0, grid = 0;
     for (const Problem &p : probs) {
         tiles += tile_count(p.d);
         cells += (long long)p.d.S * p.d.NX * p.d.NY;
         lanes += lane_cells(p.d, depth);
+        grid = std::max(grid, (long long)p.d.NX * p.d.NY);
     }
     const bool tiled = depth == kDepthSmall ? tiles <= 4096 || lanes >= 1000 * tiles
                                             : use_tiles(depth, false, cells, lanes, tiles);
     for (Problem &p : probs) {
         p.L.depth = depth;
+        p.L.far = far_stores(cells, grid);
         if (rows > 0)
             fixed_bands(p.L, rows, depth);
         else if (tiled)

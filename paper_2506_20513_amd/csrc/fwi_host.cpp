@@ -157,8 +157,8 @@ double adj_waves(int depth) { return depth == kDepthLarge ? 3.0 : 4.0; }
 //   1000 x 1000, 12              2268   2.71  2.25    11.33  9.96
 // against depth 4: per 96 steps, 2.45 us per tile of a gradient and 0.9 ns per cell plus
 // 2.15 ms of latency for streams, 0.58, 0.2 and 0.8 traces only, and from a fit of 2050
-// (2200) cells tiles however many; traces only, tiles of a lesser fit up to 3500 of
-// them (740 x 540, 20 shots: 1.85, 1.93).
+// cells tiles however many; traces only, that fit from 12 M cells on and 2200 below (740
+// x 540, 20 / 32 shots: 1.85, 1.93 / 3.14, 2.99), and of a lesser one up to 3500 tiles.
 //
 // At depth 8 (grids of 2^20 cells and more) up to 4000 tiles, and beyond by the share of
 // the streams' lanes that is grid (`lanes`: their cells, pairs of strips padded):
@@ -171,7 +171,9 @@ bool use_tiles(int depth, bool traces_only, long long cells, long long lanes, lo
     if (depth == kDepthLarge)
         return tiles <= 4000 || (tiles <= 5800 && wide >= 2150) || (tiles <= 8000 && wide >= 2400);
     const double kc = (double)cells * 1e-3;
-    if (traces_only) return per >= 2200 || (tiles <= 3500 && 0.58 * t - 0.2 * kc < 800);
+    if (traces_only)
+        return per >= (cells >= 12000000 ? 2050 : 2200) ||
+               (tiles <= 3500 && 0.58 * t - 0.2 * kc < 800);
     return per >= 2050 || 2.45 * t - 0.9 * kc < 2150;
 }
 
@@ -180,6 +182,18 @@ long long lane_cells(const Dims &d, int depth) {
     const int OW = 64 - 2 * depth, pair = depth == kDepthLarge ? 2 : 1;
     const long long strips = (d.NX + OW - 1) / OW, even = (strips + pair - 1) / pair * pair;
     return even * OW * d.NY * d.S;
+}
+
+// Whether the streaming sweep stores its fields past the caches: once those of all
+// shots, 24 bytes per cell for the two states, leave no part of themselves in them;
+// many shots of a small grid do so earlier.  (Stores that do, in us per call of 96
+// steps, traces only, against plain ones: 740 x 540, 24 shots, 9.6 M cells, 2497 and
+// 2042; 1000 x 1000, 7 shots, 1829, 1558; 900 x 1100, 10 shots, 2361, 2225; 740 x 540,
+// 100 shots, 40 M, 9670, 9627; 2088 x 1064, 32 shots, 71 M, 9141, 9272; 64 shots, 142 M,
+// 15882, 16492; 552 x 296, 48 shots, 7.8 M, 2285, 2108; 150 shots, 24.5 M, 5993, 6230;
+// 100 x 100, 900 shots, 9 M, 3270, 3423.)
+bool far_stores(long long cells, long long grid) {
+    return cells >= 32LL << 20 || (cells >= 9000000 && grid <= 1 << 18);
 }
 
 long long tile_count(const Dims &d) {
@@ -218,6 +232,7 @@ void set_streams(Layout &L, int groups) {
 // that they run in side by side: every group of a call makes the call's choice.
 void make_tiling(const Dims &all, Layout &L, int groups) {
     const long long cells = (long long)all.S * all.NX * all.NY, tiles = tile_count(all);
+    L.far = far_stores(cells, (long long)all.NX * all.NY);
     if (use_tiles(L.depth, L.mode == FWI_SAVE_NONE, cells, lane_cells(all, L.depth), tiles))
         set_tiles(L, pick_tile(tiles));
     else
@@ -493,6 +508,7 @@ Tiling tiling(const Ptrs &P) {
     t.nband = L.nband;
     t.depth = L.pass;
     t.tile = L.tile;
+    t.far = L.tile ? 0 : L.far;
     return t;
 }
 

@@ -23,12 +23,14 @@ int choose_k(const Dims &d, int depth);
 void make_tiling(const Dims &all, Layout &L, int groups = 1);
 // Whether a call of that many cells, streaming lanes' cells and tiles of the large
 // height (over all shots) runs on tiles; a problem's such lanes' cells and tiles; the
-// height for that many tiles in flight; tiles of height `rows` for both kernels; the
-// streaming decomposition.
+// height for that many tiles in flight; whether the streaming sweep's stores of that
+// many cells, on grids of at most `grid` cells, pass the caches by; tiles of height
+// `rows` for both kernels; the streaming decomposition.
 bool use_tiles(int depth, bool traces_only, long long cells, long long lanes, long long tiles);
 long long lane_cells(const Dims &d, int depth);
 long long tile_count(const Dims &d);
 int pick_tile(long long tiles);
+bool far_stores(long long cells, long long grid);
 void set_tiles(Layout &L, int rows);
 void set_streams(Layout &L, int groups = 1);
 // Row bands of height `rows` for both kernels (batched plans).

@@ -62,6 +62,7 @@ struct Layout {
                        // that the imaging sums group by
     int pass;          // most levels per pass: depth, or kTileLevels with tiles
     int tile;          // tile height of the tile kernels, 0: streaming kernels
+    int far;           // 1: the streaming sweep stores its fields past the caches
     int ncp;           // number of checkpoints
     int nslots;        // Ez slots
     // streaming decomposition (see Tiling): row bands of the forward kernel
@@ -123,6 +124,7 @@ struct Tiling {
     int depth;                // most levels per pass: kDepthSmall or kDepthLarge
                               // (streaming), kTileLevels (tiles)
     int tile;                 // tile height of the tile kernels; 0: streaming
+    int far;                  // 1: the sweep's stores past the caches (streaming)
 };
 
 // Per-call constants of the stencil kernels that only rare branches read
@@ -225,7 +227,7 @@ unsigned stream_blocks(int S, const Tiling &tl);
 // every problem of the launch; tail (streaming): the problems advance fewer
 // than depth levels.  lev (forward only): 1 if every
 // problem's entry has E_lev set (segment re-forward), 0 if none has.
-inline int table_depth(const Tiling &tl) { return tl.depth | tl.tile << 8; }
+inline int table_depth(const Tiling &tl) { return tl.depth | tl.far << 4 | tl.tile << 8; }
 hipError_t launch_fwd_table(const FwdStreamArgs *tab, const unsigned *boff, int nm,
                             unsigned nblocks, int depth, bool tail, int lev, hipStream_t st);
 hipError_t launch_adj_table(const AdjStreamArgs *tab, const unsigned *boff, int nm,

@@ -105,8 +105,10 @@ __device__ __forceinline__ WaveTile wave_tile(const Tiling &tl, int S, int NX, i
 // psi is a float4 (psi_hx, psi_hy, psi_ex, psi_ey).  LEV: 1 if the pass
 // writes every level's Ez (a.E_lev set), 0 if only the final state; fixing
 // the choice at compile time keeps the other stores' addresses out of the
-// scalar registers.
-template <int K, bool EDGE, bool TAIL, int LEV>
+// scalar registers.  FAR: the final fields' stores pass the caches by, as those of every
+// level's Ez always do (a template parameter as well: two stores that a branch chooses
+// between are merged to a plain one).
+template <int K, bool EDGE, bool TAIL, bool FAR, int LEV>
 __device__ __forceinline__ void fwd_body(const FwdStreamArgs &a, const WaveTile &w,
                                          float4 (*ring)[64]) {
     constexpr int OW = 64 - 2 * K;
@@ -138,6 +140,11 @@ __device__ __forceinline__ void fwd_body(const FwdStreamArgs &a, const WaveTile 
     const int rlast = min(NY - 1, y1 + nlev - 1);
     static_assert(LEV == 0 || LEV == 1, "LEV is 0 or 1");
     const bool lev = LEV == 1;
+    auto put = [](float *base, unsigned k, float v) {
+        if (FAR) stg_nt(base, k, v);
+        else stg(base, k, v);
+    };
+    static_assert(!(FAR && LEV), "only the sweep chooses");
     float *const elev0 = lev ? a.E_lev + so : nullptr;   // level 0 slot of the shot
     const size_t lstr = a.lev_stride;
 
@@ -251,16 +258,15 @@ __device__ __forceinline__ void fwd_body(const FwdStreamArgs &a, const WaveTile 
             }
             if (jown && own) {
                 const unsigned k = (unsigned)(j * P + i);
-                // Streamed fields pass the caches by (2048 x 1024, 64 shots, per
-                // pass: history 2.62 -> 2.30 ms, the sweep's fields 1.42 -> 1.38),
-                // but not where they go with the history (2.30 -> 2.37), nor do
-                // the adjoint's stores and loads (2.98 -> 3.3 ms and more).
+                // every level's Ez is not read again soon (2048 x 1024, 64 shots: 2.62 ->
+                // 2.30 ms per pass; never slower from 2 M cells on); the H fields and
+                // CPML memories that go with it are, by the next pass (2.30 -> 2.37)
                 if (lev) stg_nt(el, k, e);
                 if (last) {
                     if (!lev) {
-                        stg_nt(a.E_out + so, k, e);
-                        stg_nt(a.Hx_out + so, k, hx);
-                        stg_nt(a.Hy_out + so, k, hy);
+                        put(a.E_out + so, k, e);
+                        put(a.Hx_out + so, k, hx);
+                        put(a.Hy_out + so, k, hy);
                     } else {
                         stg(a.Hx_out + so, k, hx);
                         stg(a.Hy_out + so, k, hy);
@@ -303,7 +309,7 @@ __device__ __forceinline__ void fwd_body(const FwdStreamArgs &a, const WaveTile 
     }
 }
 
-template <int K, bool TAIL, int LEV>
+template <int K, bool TAIL, bool FAR, int LEV>
 __global__ __launch_bounds__(64 * BlockStrips<K>::n) void k_fwd(FwdStreamArgs a) {
     static_assert((K & (K - 1)) == 0, "K must be a power of two");
     constexpr int NS = BlockStrips<K>::n;
@@ -313,9 +319,9 @@ __global__ __launch_bounds__(64 * BlockStrips<K>::n) void k_fwd(FwdStreamArgs a)
     if (!w.valid) return;
     float4 (*wr)[64] = ring[NS > 1 ? wave_in_block() : 0];
     if (w.edge)
-        fwd_body<K, true, TAIL, LEV>(a, w, wr);
+        fwd_body<K, true, TAIL, FAR, LEV>(a, w, wr);
     else
-        fwd_body<K, false, TAIL, LEV>(a, w, wr);
+        fwd_body<K, false, TAIL, FAR, LEV>(a, w, wr);
 }
 
 // LEV as in fwd_body, 0 or 1: the problems of one launch all write every
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(64 * BlockStrips<K>::n) void k_fwd(FwdStreamArgs a)
 // table stay live in registers where kernel arguments would be reloaded, so
 // the depth-4 sweep would need 102 VGPRs (4 waves per SIMD); it is held to
 // 5 waves, which it reaches without spilling.
-template <int K, bool TAIL, int LEV>
+template <int K, bool TAIL, bool FAR, int LEV>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(K == kDepthSmall && LEV == 0
                                                                         ? 5
                                                                         : 1))) void
@@ -334,9 +340,9 @@ k_fwd_tab(const FwdStreamArgs *tab, const unsigned *boff, int nm) {
     const FwdStreamArgs a = load_const(tab, m);
     const WaveTile w = wave_tile<K>(a.tl, a.S, a.NX, a.npml, (int)(lb - ldc(boff, m)));
     if (w.edge)
-        fwd_body<K, true, TAIL, LEV>(a, w, ring);
+        fwd_body<K, true, TAIL, FAR, LEV>(a, w, ring);
     else
-        fwd_body<K, false, TAIL, LEV>(a, w, ring);
+        fwd_body<K, false, TAIL, FAR, LEV>(a, w, ring);
 }
 
 // ---------------------------------------------------------------------------
@@ -620,24 +626,15 @@ unsigned stream_blocks(int S, const Tiling &tl) {
     return (unsigned)S * tl.nstrip * tl.nband;
 }
 
-template <int K, int LEV>
-void launch_fwd_table_lev(const FwdStreamArgs *tab, const unsigned *boff, int nm,
-                          unsigned nblocks, bool tail, hipStream_t st) {
-    if (tail)
-        hipLaunchKernelGGL((k_fwd_tab<K, true, LEV>), dim3(nblocks), dim3(64), 0, st, tab, boff,
-                           nm);
-    else
-        hipLaunchKernelGGL((k_fwd_tab<K, false, LEV>), dim3(nblocks), dim3(64), 0, st, tab, boff,
-                           nm);
-}
-
 template <int K>
 hipError_t launch_fwd_table_depth(const FwdStreamArgs *tab, const unsigned *boff, int nm,
-                                  unsigned nblocks, bool tail, int lev, hipStream_t st) {
-    if (lev == 0)
-        launch_fwd_table_lev<K, 0>(tab, boff, nm, nblocks, tail, st);
-    else
-        launch_fwd_table_lev<K, 1>(tab, boff, nm, nblocks, tail, st);
+                                  unsigned nblocks, bool tail, int lev, bool far,
+                                  hipStream_t st) {
+    auto kernel = lev ? (tail ? k_fwd_tab<K, true, false, 1> : k_fwd_tab<K, false, false, 1>)
+                  : tail ? k_fwd_tab<K, true, false, 0>
+                  : far  ? k_fwd_tab<K, false, true, 0>
+                         : k_fwd_tab<K, false, false, 0>;
+    hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64), 0, st, tab, boff, nm);
     return hipGetLastError();
 }
 
@@ -656,10 +653,11 @@ hipError_t launch_fwd_table(const FwdStreamArgs *tab, const unsigned *boff, int 
     if (lev != 0 && lev != 1) return hipErrorInvalidValue;
     if (nblocks == 0) return hipSuccess;
     if (depth >> 8) return launch_fwd_tile_table(tab, boff, nm, nblocks, depth >> 8, lev, st);
-    if (depth == kDepthSmall)
-        return launch_fwd_table_depth<kDepthSmall>(tab, boff, nm, nblocks, tail, lev, st);
-    if (depth == kDepthLarge)
-        return launch_fwd_table_depth<kDepthLarge>(tab, boff, nm, nblocks, tail, lev, st);
+    const bool far = depth >> 4 & 1;
+    if ((depth & 15) == kDepthSmall)
+        return launch_fwd_table_depth<kDepthSmall>(tab, boff, nm, nblocks, tail, lev, far, st);
+    if ((depth & 15) == kDepthLarge)
+        return launch_fwd_table_depth<kDepthLarge>(tab, boff, nm, nblocks, tail, lev, far, st);
     return hipErrorInvalidValue;
 }
 
@@ -667,9 +665,9 @@ hipError_t launch_adj_table(const AdjStreamArgs *tab, const unsigned *boff, int 
                             unsigned nblocks, int depth, bool tail, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
     if (depth >> 8) return launch_adj_tile_table(tab, boff, nm, nblocks, depth >> 8, st);
-    if (depth == kDepthSmall)
+    if ((depth & 15) == kDepthSmall)
         return launch_adj_table_depth<kDepthSmall>(tab, boff, nm, nblocks, tail, st);
-    if (depth == kDepthLarge)
+    if ((depth & 15) == kDepthLarge)
         return launch_adj_table_depth<kDepthLarge>(tab, boff, nm, nblocks, tail, st);
     return hipErrorInvalidValue;
 }
@@ -686,19 +684,13 @@ unsigned single_blocks(int S, const Tiling &tl) {
 // nlev < depth takes the partial-pass variant.
 template <int K>
 hipError_t launch_fwd_depth(const FwdStreamArgs &a, hipStream_t st) {
-    const unsigned nb = single_blocks<K>(a.S, a.tl);
-    const bool full = a.nlev == K;
-    if (a.E_lev) {
-        if (full)
-            hipLaunchKernelGGL((k_fwd<K, false, 1>), dim3(nb), dim3(64 * BlockStrips<K>::n), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_fwd<K, true, 1>), dim3(nb), dim3(64 * BlockStrips<K>::n), 0, st, a);
-    } else {
-        if (full)
-            hipLaunchKernelGGL((k_fwd<K, false, 0>), dim3(nb), dim3(64 * BlockStrips<K>::n), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_fwd<K, true, 0>), dim3(nb), dim3(64 * BlockStrips<K>::n), 0, st, a);
-    }
+    const bool tail = a.nlev != K;
+    auto kernel = a.E_lev    ? (tail ? k_fwd<K, true, false, 1> : k_fwd<K, false, false, 1>)
+                  : tail     ? k_fwd<K, true, false, 0>
+                  : a.tl.far ? k_fwd<K, false, true, 0>
+                             : k_fwd<K, false, false, 0>;
+    hipLaunchKernelGGL(kernel, dim3(single_blocks<K>(a.S, a.tl)), dim3(64 * BlockStrips<K>::n), 0,
+                       st, a);
     return hipGetLastError();
 }
 

@@ -59,7 +59,7 @@ def kernel_source_hash() -> str:
 
 def short_name(name: str) -> str | None:
     """The benchmark's name for a kernel of a trace: the single-problem
-    forward kernels k_fwd<K, TAIL, LEV> and k_fwd_tile<D, R, NW, LEV> are
+    forward kernels k_fwd<K, TAIL, FAR, LEV> and k_fwd_tile<D, R, NW, LEV> are
     k_fwd_sweep for LEV = 0 (only the final state written) and
     k_fwd_reforward for LEV = 1 (every level's Ez written), k_adj_tile is
     k_adj; other kernels keep their own name."""

@@ -53,3 +53,32 @@ def test_measured_calls_take_the_faster_kernels(route, NX, NY, S, gradient, trac
     assert route(NX, NY, S, GRADIENT) == gradient
     assert route(NX, NY, S, CHECKPOINT) == route(NX, NY, S, HISTORY) == gradient
     assert route(NX, NY, S, NONE) == traces
+
+
+FAR_CODE = """
+#include "fwi_host.h"
+#include <cstring>
+using namespace fwi;
+using namespace fwi::host;
+static char ws[1 << 20];
+extern "C" int far_of(int NX, int NY, int S, int mode) {
+    Dims d{};
+    d.NX = NX; d.NY = NY; d.npml = 10; d.nt = 96; d.S = S; d.R = 4;
+    d.pitch = (NX + 63) / 64 * 64; d.W = d.Hs = 21;
+    d.plane = (size_t)NY * d.pitch; d.xs = (size_t)NY * d.W; d.ys = (size_t)d.Hs * d.pitch;
+    Layout L;
+    if (make_layout(d, mode, L) != FWI_OK) return -1;
+    const Tiling t = fwd_args(Ptrs{ws, &L}).tl;
+    return t.tile ? 2 : t.far;
+}
+"""
+
+
+def test_only_large_sweeps_store_past_the_caches(tmp_path):
+    """2: tiles; else whether the streaming sweep's stores pass the caches by, which
+    costs it up to a fifth where the caches hold a part of its fields."""
+    f = build(tmp_path, "far", FAR_CODE).far_of
+    assert [f(740, 540, 24, NONE), f(552, 296, 48, NONE), f(2088, 1064, 8, NONE)] == [0, 0, 0]
+    assert [f(2088, 1064, 64, m) for m in (NONE, GRADIENT)] == [1, 1]
+    assert f(100, 100, 900, NONE) == f(552, 296, 150, NONE) == 1
+    assert f(552, 296, 24, GRADIENT) == 2 and f(552, 296, 48, GRADIENT) == 0
