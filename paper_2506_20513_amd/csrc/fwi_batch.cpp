@@ -62,6 +62,8 @@ struct Step {
     int depth;                     // temporal depth of a stencil step
     int lev;                       // forward steps: 1 if the entries write every
                                    // level's Ez (segment re-forward), 0 if not
+    int levels = 0;                // stencil steps: most levels of an entry
+    bool full = false;             // and whether every entry has a whole pass of them
     int nm;
     unsigned nblocks;
     unsigned long long ctotal;     // copy steps: floats copied
@@ -352,6 +354,7 @@ void build_schedule(std::vector<Problem> &probs, char *ws, size_t area, Schedule
             Step s;
             s.kind = o.kind;
             s.tail = tail != 0;
+            s.full = true;
             s.depth = table_depth(ot);
             s.lev = lev;
             s.nm = 0;
@@ -369,6 +372,8 @@ void build_schedule(std::vector<Problem> &probs, char *ws, size_t area, Schedule
                 const Tiling &tl = q.kind == OP_FWD ? q.fa.tl : q.aa.tl;
                 const int Sq = q.kind == OP_FWD ? q.fa.S : q.aa.S;
                 s.nblocks += stream_blocks(Sq, tl);
+                s.levels = std::max(s.levels, nlev);
+                s.full = s.full && nlev == depth;
                 S.boff.push_back(s.nblocks);
                 if (q.kind == OP_FWD) S.ftab.push_back(q.fa); else S.atab.push_back(q.aa);
                 ++s.nm;
@@ -564,10 +569,10 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
         // time, for every candidate, the largest merged full-depth launch of
         // each pass kind (best of 3 each): the forward sweep, the segment
         // re-forward and the adjoint.  A gradient runs one of each per
-        // pass (`depth` steps, or a tile pass's levels), so the cost per step is
-        // (sweep + re-forward + adjoint) / those.  The largest launches are those where every
+        // pass, so the cost per step is the sum of the three, each divided by the
+        // levels it advanced.  The largest launches are those where every
         // problem takes part; the first adjoint launches hold only the
-        // longest problems.  The re-forward and adjoint passes run on
+        // longest problems, and what is left of their windows over whole passes.  The re-forward and adjoint passes run on
         // whatever state the workspace holds (all of it allocated); their
         // time does not depend on the values, and every run of the plan
         // clears that state first.
@@ -626,7 +631,8 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
                     ++first;
                 }
                 // largest full-depth launch of a kind (forward: of a
-                // level-store choice), else the largest partial one
+                // level-store choice), else the largest partial one (tiles take
+                // every number of levels in one launch)
                 auto largest = [&](OpKind kind, int lev) {
                     size_t best_k = S.steps.size();
                     for (size_t k = first; k < S.steps.size(); ++k) {
@@ -637,9 +643,7 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
                             continue;
                         }
                         const Step &b = S.steps[best_k];
-                        if ((b.tail && !q.tail) ||
-                            (b.tail == q.tail && q.nblocks > b.nblocks))
-                            best_k = k;
+                        if (q.full != b.full ? q.full : q.nblocks > b.nblocks) best_k = k;
                     }
                     return best_k;
                 };
@@ -649,13 +653,13 @@ extern "C" int fwi_batch_plan_create(int32_t n, const fwi_batch_problem *problem
                     rc = rc == FWI_OK ? FWI_EHIP : rc;
                     break;
                 }
-                float tf = 0.f, tr = 0.f, ta = 0.f;
-                rc = time_step(S.steps[fsw], tf);
-                if (rc == FWI_OK && fre < S.steps.size()) rc = time_step(S.steps[fre], tr);
-                else tr = tf;
-                if (rc == FWI_OK) rc = time_step(S.steps[fadj], ta);
+                double cost = 0.0;
+                for (size_t k : {fsw, fre < S.steps.size() ? fre : fsw, fadj}) {
+                    float ms = 0.f;
+                    if (rc == FWI_OK) rc = time_step(S.steps[k], ms);
+                    cost += (double)ms / S.steps[k].levels;
+                }
                 if (rc != FWI_OK) break;
-                const double cost = ((double)tf + tr + ta) / probs.front().L.pass;
                 if (probs.front().L.tile) tile_cost = cost;
                 consider(dep, h, cost);
             }
