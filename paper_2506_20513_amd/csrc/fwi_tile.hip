@@ -88,6 +88,16 @@ __device__ __forceinline__ float pick(const float (&a)[R], int r) {
     return v;
 }
 
+// The workgroup's barrier of a level.  The waves of a workgroup pass it in bodies of
+// their own (by_kind): the language's barrier asks for one that all threads reach, so
+// this one is written as what the hardware has, where s_barrier counts the waves that
+// have reached any of them.  Every wave passes it once per level, in whichever body.
+__device__ __forceinline__ void level_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // f(x-direction CPML in the tile, y-direction CPML in the wave's rows)
 template <class F>
 __device__ __forceinline__ void by_kind(const TileGeom &g, F &&f) {
@@ -289,7 +299,7 @@ __device__ __forceinline__ void fwd_tile_kind(const FwdStreamArgs &a, const Tile
         xch[b][g.wave][0][lane] = f.E[0];
         xch[b][g.wave][1][lane] = f.E[R - 1];
         const float w = src ? ldc(wav, l) : 0.f;
-        __syncthreads();
+        level_barrier();
         const float eup = g.wave > 0 ? xch[b][g.wave - 1][1][lane] : 0.f;
         const float edn = g.wave < NW - 1 ? xch[b][g.wave + 1][0][lane] : 0.f;
         if (rmask) record(l);                        // stage 1
@@ -337,8 +347,8 @@ __device__ __forceinline__ void fwd_tile_kind(const FwdStreamArgs &a, const Tile
 
 // Each kind of wave (tile with or without x-direction CPML columns, rows with
 // or without y-direction CPML) runs a body of its own from the loads to the
-// stores: nothing per lane is live where they part.  All have the same
-// barriers.
+// stores: nothing per lane is live where they part.  All pass as many barriers
+// (level_barrier).
 template <int D, int R, int NW, int LEV>
 __device__ __forceinline__ void fwd_tile(const FwdStreamArgs &a, int blk) {
     __shared__ float xch[2][NW][2][64];
@@ -546,7 +556,7 @@ __device__ __forceinline__ void adj_tile_kind(const AdjStreamArgs &a, const Tile
             const int b = l & 1, n = a.n_top - 1 - l;
             xch[b][g.wave][0][lane] = f.L[0];
             xch[b][g.wave][1][lane] = f.L[R - 1];
-            __syncthreads();
+            level_barrier();
             const float lup = g.wave > 0 ? xch[b][g.wave - 1][1][lane] : 0.f;
             const float ldn = g.wave < NW - 1 ? xch[b][g.wave + 1][0][lane] : 0.f;
             if (sadj && slane)
