@@ -355,7 +355,7 @@ void build_schedule(std::vector<Problem> &probs, char *ws, size_t area, Schedule
             s.kind = o.kind;
             s.tail = tail != 0;
             s.full = true;
-            s.depth = table_depth(ot);
+            s.depth = table_depth(ot, o.kind == OP_FWD && o.fa.far);
             s.lev = lev;
             s.nm = 0;
             s.nblocks = 0;

@@ -88,7 +88,10 @@ int stream_depth(const Dims &d) {
 
 // Checkpoint interval minimising checkpoints + segment buffer,
 // ceil(nt/K) * C + (K+1) * E with C one full state and E one Ez slot, rounded
-// to a multiple of the temporal depth so segments split into full passes.
+// to a multiple of the streaming depth, so that segments split into full streaming
+// passes.  Tile passes advance kTileLevels steps: at an odd multiple of depth 4 a
+// segment's last pass holds half of them (K = 52 for 800 steps: 6 full passes and a
+// half).  The interval fixes the workspace's size, which the queries return.
 int choose_k(const Dims &d, int depth) {
     const double C = 3.0 * d.plane + 2.0 * d.xs + 2.0 * d.ys;
     const double E = (double)d.plane;
@@ -508,7 +511,6 @@ Tiling tiling(const Ptrs &P) {
     t.nband = L.nband;
     t.depth = L.pass;
     t.tile = L.tile;
-    t.far = L.tile ? 0 : L.far;
     return t;
 }
 
@@ -550,6 +552,7 @@ FwdStreamArgs fwd_args(const Ptrs &P) {
     a.NX = d.NX; a.NY = d.NY; a.npml = d.npml; a.pitch = d.pitch;
     a.W = d.W; a.S = d.S; a.R = d.R; a.nt = d.nt;
     a.n = 0; a.nlev = 0; a.record = 0;
+    a.far = L.tile ? 0 : L.far;
     a.tl = tiling(P);
     a.plane = d.plane; a.xs = d.xs; a.ys = d.ys;
     a.lev_stride = (size_t)d.S * d.plane;
@@ -800,9 +803,10 @@ int do_adjoint(const Layout &L, const float *eps_r, const float *sigma, float *g
     int acur = 0;
     const double all = (double)d.NX * d.NY * d.S;
     // adjoint passes over steps [n_lo, n_hi), the forward Ez^{n_lo + k} in slot k.
-    // Every pass starts at a multiple of the streaming depth (a partial pass
-    // first, at the top), so the grouping of the imaging sums, and with it
-    // every rounding, is the same for any checkpoint interval.
+    // Every pass ends at a multiple of its length or at the segment's start (a
+    // partial pass first, at the top), and the imaging sums group by the streaming
+    // depth, of which both are multiples: their grouping, and with it every
+    // rounding, is the same for any checkpoint interval, on tiles and streams.
     auto adj_range = [&](int n_hi, int n_lo) -> int {
         for (int n_top = n_hi; n_top > n_lo; n_top -= a.nlev) {
             a.nlev = n_top - std::max(n_lo, (n_top - 1) / L.pass * L.pass);

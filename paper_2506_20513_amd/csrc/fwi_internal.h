@@ -124,7 +124,6 @@ struct Tiling {
     int depth;                // most levels per pass: kDepthSmall or kDepthLarge
                               // (streaming), kTileLevels (tiles)
     int tile;                 // tile height of the tile kernels; 0: streaming
-    int far;                  // 1: the sweep's stores past the caches (streaming)
 };
 
 // Per-call constants of the stencil kernels that only rare branches read
@@ -145,6 +144,7 @@ struct FwdStreamArgs {
     int NX, NY, npml, pitch, W, S, R, nt;
     int n, nlev;              // first step of the pass, steps in the pass (<= K)
     int record;               // write traces
+    int far;                  // 1: the sweep's stores past the caches (streaming)
     Tiling tl;
     size_t plane, xs, ys, lev_stride;
     float ch, rdx, rdy, src_scale;
@@ -223,11 +223,13 @@ hipError_t launch_adj_stream(const AdjStreamArgs &a, hipStream_t st);
 unsigned stream_blocks(int S, const Tiling &tl);
 // One pass for nm problems at once: tab[m] (device) holds problem m's
 // arguments and boff[0..nm] (device) the prefix sums of their block counts,
-// nblocks = boff[nm].  depth: table_depth of the passes' tiling, the same for
+// nblocks = boff[nm].  depth: table_depth of the passes' tiling (and far), the same for
 // every problem of the launch; tail (streaming): the problems advance fewer
 // than depth levels.  lev (forward only): 1 if every
 // problem's entry has E_lev set (segment re-forward), 0 if none has.
-inline int table_depth(const Tiling &tl) { return tl.depth | tl.far << 4 | tl.tile << 8; }
+inline int table_depth(const Tiling &tl, bool far = false) {
+    return tl.depth | (int)far << 4 | tl.tile << 8;
+}
 hipError_t launch_fwd_table(const FwdStreamArgs *tab, const unsigned *boff, int nm,
                             unsigned nblocks, int depth, bool tail, int lev, hipStream_t st);
 hipError_t launch_adj_table(const AdjStreamArgs *tab, const unsigned *boff, int nm,

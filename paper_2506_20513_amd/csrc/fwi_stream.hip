@@ -685,10 +685,10 @@ unsigned single_blocks(int S, const Tiling &tl) {
 template <int K>
 hipError_t launch_fwd_depth(const FwdStreamArgs &a, hipStream_t st) {
     const bool tail = a.nlev != K;
-    auto kernel = a.E_lev    ? (tail ? k_fwd<K, true, false, 1> : k_fwd<K, false, false, 1>)
-                  : tail     ? k_fwd<K, true, false, 0>
-                  : a.tl.far ? k_fwd<K, false, true, 0>
-                             : k_fwd<K, false, false, 0>;
+    auto kernel = a.E_lev ? (tail ? k_fwd<K, true, false, 1> : k_fwd<K, false, false, 1>)
+                  : tail  ? k_fwd<K, true, false, 0>
+                  : a.far ? k_fwd<K, false, true, 0>
+                          : k_fwd<K, false, false, 0>;
     hipLaunchKernelGGL(kernel, dim3(single_blocks<K>(a.S, a.tl)), dim3(64 * BlockStrips<K>::n), 0,
                        st, a);
     return hipGetLastError();

@@ -68,8 +68,8 @@ extern "C" int far_of(int NX, int NY, int S, int mode) {
     d.plane = (size_t)NY * d.pitch; d.xs = (size_t)NY * d.W; d.ys = (size_t)d.Hs * d.pitch;
     Layout L;
     if (make_layout(d, mode, L) != FWI_OK) return -1;
-    const Tiling t = fwd_args(Ptrs{ws, &L}).tl;
-    return t.tile ? 2 : t.far;
+    const FwdStreamArgs a = fwd_args(Ptrs{ws, &L});
+    return a.tl.tile ? 2 : a.far;
 }
 """
 
