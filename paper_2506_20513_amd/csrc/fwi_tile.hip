@@ -18,13 +18,14 @@
 // latency per row of the march (29.5 us per 4-step launch on 148 x 148 cells,
 // one shot); here all loads of a tile are in flight together and the levels
 // run without touching memory, at the price of a halo on all four sides.  A
-// pass of 8 steps on that grid takes 10.3 us: 5.7 us launch, loads and stores,
+// pass of 8 steps on that grid takes 9.7 us: about 4 us launch, loads and stores,
 // then 0.7 us per level, bound by the vector instructions of a tile on its CU.
-// On 552 x 296 cells x 24 shots a sweep of 8 steps takes 79 us, half of it
-// vector instructions, the rest latency that one workgroup of 16 waves per CU
-// does not hide.  Every cell sees the operations of the streaming kernels
-// in their order (the fused multiply-adds are written out and nothing else is
-// fused), so the results are the same bit for bit.
+// On 552 x 296 cells x 24 shots a sweep of 8 steps takes 82 us; a SIMD issues
+// vector instructions in two thirds of its cycles (half of them arithmetic), the
+// rest is latency that one workgroup of 16 waves per CU does not hide.  Every cell
+// sees the operations of the streaming kernels in their order (the fused
+// multiply-adds are written out and nothing else is fused), so the results are the
+// same bit for bit.
 #include "fwi_stencil.h"
 
 #include <type_traits>

@@ -20,8 +20,8 @@
 // shrink of a cell was evaluated three times (for itself and for its right and
 // lower neighbour) and 28 bytes per cell moved every iteration: 50 iterations on
 // two 1064 x 2088 fields took 1.48 ms, 20 on two 128 x 128 fields 92 us.  Now
-// 0.53 ms, bound by the vector instructions (about 45 per cell and iteration,
-// 1.6 times for the halo: 0.40 ms at the full rate), and 28 us, bound by three
+// 0.54 ms, bound by the vector instructions (about 45 per cell and iteration,
+// 1.6 times for the halo: 0.40 ms at the full rate), and 27 us, bound by three
 // launches and the serial iterations of a tile.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
